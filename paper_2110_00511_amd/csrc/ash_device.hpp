@@ -183,6 +183,48 @@ __device__ __forceinline__ uint32_t home_slot(const TableRef& tb, uint64_t h) {
 }
 
 // ---------------------------------------------------------------------------
+// Key sources: map keys read from the batch, or voxel keys computed from
+// points.  load() returns false for a point that is rejected.
+template <int KD>
+struct BatchKeys {
+  const int32_t* __restrict__ keys;
+  __device__ __forceinline__ bool load(uint32_t p, int32_t (&k)[KD]) const {
+    const int32_t* r = keys + (size_t)p * KD;
+#pragma unroll
+    for (int d = 0; d < KD; ++d) k[d] = r[d];
+    return true;
+  }
+};
+
+// Listing 1 of Sec. 6.1: floor(xyz / voxel_size) as int32.  The quotient is
+// the correctly rounded binary32 division (the build keeps IEEE division and
+// denormals); NaN, infinities and floors outside int32 fail the range test.
+struct VoxelKeys {
+  const float* __restrict__ points;
+  float voxel;
+  __device__ __forceinline__ bool load(uint32_t p, int32_t (&k)[3]) const {
+    bool ok = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const float q = points[(size_t)p * 3 + d] / voxel;
+      const float f = floorf(q);
+      const bool in = f >= -2147483648.0f && f < 2147483648.0f;
+      ok = ok && in;
+      k[d] = in ? (int32_t)f : 0;
+    }
+    return ok;
+  }
+};
+
+template <int KD>
+__device__ __forceinline__ bool keys_equal(const int32_t (&a)[KD], const int32_t (&b)[KD]) {
+  bool eq = true;
+#pragma unroll
+  for (int d = 0; d < KD; ++d) eq = eq && a[d] == b[d];
+  return eq;
+}
+
+// ---------------------------------------------------------------------------
 // Slot access.
 template <int S>
 struct Slot {
@@ -438,6 +480,28 @@ __device__ inline void copy_rows(const ValueSet& vs, int j, const uint2* pairs, 
     default: copy_rows_t<uint8_t>(vs.src[j], vs.dst[j], vs.row_bytes[j], vs.units_log2[j], pairs, count); break;
   }
 }
+
+// ---------------------------------------------------------------------------
+// Batches split by key hash (ash_partition.hip).  n positions in nrange ranges
+// of `per`; nbins bins of whole home buckets (bin = home bucket >> shift).
+constexpr uint32_t kPartTile = 4096;     // positions whose copies are dropped together
+constexpr uint32_t kPartRanges = 256;    // most ranges
+constexpr uint32_t kPartBins = 4096;     // most bins
+constexpr uint32_t kVoxelBinMean = 3840; // most points per bin of a voxelization, on average
+// A point's link while a partitioned voxelization runs (positions < 2^30).
+constexpr uint32_t kVoxelWinner = 0x80000000u;  // + the voxel's count: the first point of its voxel
+constexpr uint32_t kVoxelLocal = 0x40000000u;   // + the position of the range's point it repeats
+
+struct PartPlan {
+  uint32_t n, nrange, per, nbins;
+  uint32_t nbuckets, shift;
+  uint32_t pos_bits;   // bits that hold a position
+  uint32_t* hist;      // [nrange][nbins]
+  uint32_t* total;     // [nbins]
+  uint32_t* base;      // [nbins + 1]: first entry of each bin
+  uint64_t* reps;      // a bit per position: it has an entry
+  uint32_t* entries;
+};
 
 // ---------------------------------------------------------------------------
 // Batched maps: one descriptor per (map, insert batch, find batch).  The

@@ -72,39 +72,7 @@ __device__ __forceinline__ const ReqDesc* stage_requests(const ReqArgs& args, co
 }
 
 // ---------------------------------------------------------------------------
-// Key sources: map keys read from the batch, or voxel keys computed from
-// points.  load() returns false for a point that is rejected.
-template <int KD>
-struct BatchKeys {
-  const int32_t* __restrict__ keys;
-  __device__ __forceinline__ bool load(uint32_t p, int32_t (&k)[KD]) const {
-    const int32_t* r = keys + (size_t)p * KD;
-#pragma unroll
-    for (int d = 0; d < KD; ++d) k[d] = r[d];
-    return true;
-  }
-};
-
-// Listing 1 of Sec. 6.1: floor(xyz / voxel_size) as int32.  The quotient is
-// the correctly rounded binary32 division (the build keeps IEEE division and
-// denormals); NaN, infinities and floors outside int32 fail the range test.
-struct VoxelKeys {
-  const float* __restrict__ points;
-  float voxel;
-  __device__ __forceinline__ bool load(uint32_t p, int32_t (&k)[3]) const {
-    bool ok = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const float q = points[(size_t)p * 3 + d] / voxel;
-      const float f = floorf(q);
-      const bool in = f >= -2147483648.0f && f < 2147483648.0f;
-      ok = ok && in;
-      k[d] = in ? (int32_t)f : 0;
-    }
-    return ok;
-  }
-};
-
+// More key sources (BatchKeys and VoxelKeys: ash_device.hpp).
 // Neighbor keys (Listing 3 of Sec. 6.2.4; the 1-cube and 1-ring lookups of
 // Sec. 6.3): position p is query p / k shifted by offset p % k, word by word
 // with int32 addition wrapping modulo 2^32.  Positions of one query are
@@ -138,14 +106,6 @@ struct ReqKeys {
     return true;
   }
 };
-
-template <int KD>
-__device__ __forceinline__ bool keys_equal(const int32_t (&a)[KD], const int32_t (&b)[KD]) {
-  bool eq = true;
-#pragma unroll
-  for (int d = 0; d < KD; ++d) eq = eq && a[d] == b[d];
-  return eq;
-}
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll

@@ -111,6 +111,16 @@ hipError_t launch_voxel_claim(int g, int w, const TableRef& tb, const float* pts
 hipError_t launch_voxel_commit(const TableRef& tb, const float* pts, float voxel, uint32_t n, uint32_t* slot_of,
                                uint8_t* lost, int32_t* voxel_keys, int32_t* counts, int32_t* point_voxel, Meta* meta,
                                uint64_t* status, hipStream_t st);
+// The ranges of a batch of n positions split by key hash (n, nrange, per and
+// pos_bits of the plan); false when positions do not fit 30 bits.
+bool part_ranges(PartPlan* pl, uint32_t n);
+// A whole voxelization by hash bins: the plan's n / nbins must be at most
+// 2 * kVoxelBinMean; link is n words, status a word pair per 1024 points (both
+// need no initial state).  Writes what launch_voxel_commit and
+// launch_voxel_resolve write; meta->claims is the number of voxels.
+hipError_t launch_voxel_partitioned(const PartPlan& pl, const float* pts, float voxel, uint32_t* link,
+                                    int32_t* voxel_keys, int32_t* counts, int32_t* point_voxel, Meta* meta,
+                                    uint64_t* status, hipStream_t st);
 // Per point: block keys, in-block voxel coordinates (res >= 1) and a valid flag.
 hipError_t launch_block_coords(const float* pts, uint32_t n, float voxel, int32_t res, int32_t* block_keys,
                                int32_t* local, uint8_t* valid, hipStream_t st);
