@@ -225,6 +225,81 @@ ValueSet make_values(const ash_map* m, const void* const* src, void* const* dst,
   return vs;
 }
 
+// An insert into an empty map goes by hash bins (ash_partition.hip) from this
+// many positions on, where the table is at most kPartTableRatio times as large
+// (its parts are written whole) and enough of the positions bring new keys:
+// that path does the same for a new key as for a repeat, while the general path
+// spends a CAS and a random store on each new key and little on a repeat.
+// Clear + insert, general path against bins, int32x3 keys, W = 2, one lane per key:
+//   1M positions, half new 97 / 91 us, 2M 149 / 143, 4M 302 / 235, 10M 712 / 543;
+//   10M, 10% new 396 / 468, 20% 495 / 504, 30% 587 / 505, 99% 984 / 569;
+//   2.1M, 20% new 125 / 137, 40% 151 / 145, 99% 212 / 159.
+// Key width 4 moves entries of 32 bytes: 4M, 45% new 332 / 344, 99% 487 / 371.
+// Into a table that holds keys, every key has to be looked up in it too: a
+// second insert of 2.7M takes 242 / 275 us, of 10M 957 / 835 with W = 2 and
+// 896 / 921 with W = 4, four lanes per key, all new, and 849 / 857 and
+// 827 / 964 half new; so only the empty table's goes by bins.  An erase by bins
+// (lookups, no new keys' stores) took 438 against 379 us for 5M.
+// The last finalized insert's fraction decides; where there was none, widths
+// 1 to 3 go by bins (a first insert cannot keep its pending keys either: 10M
+// with 10% new take about 530 us on the general path then).
+constexpr int64_t kInsertPartMin = 5 << 19;
+constexpr int64_t kPartTableRatio = 8;
+
+bool insert_by_bins(const ash_map* m, int64_t n, uint64_t last_n, uint64_t last_new) {
+  if (m->used_ub > 0) return false;
+  if (n < kInsertPartMin || (int64_t)m->nslots > kPartTableRatio * n) return false;
+  if (m->key_dim == 4) return last_n > 0 && last_new * 10 >= last_n * 8;
+  return last_n == 0 || last_new * 100 > last_n * 35;
+}
+
+// The plan and workspace of a batch of n positions by hash bins on m's table;
+// false when it does not fit the plan's limits or its workspace cannot be had
+// (the general path then runs).
+bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hipStream_t st) {
+  if (n > (int64_t)ash::kPartRanges * ash::kPartMostPer) return false;
+  std::memset(pl, 0, sizeof(*pl));
+  if (!ash::part_ranges(pl, (uint32_t)n) || pl->per > ash::kPartMostPer) return false;
+  if (!ash::part_buckets(pl, m->nslots / (uint32_t)m->W, (uint32_t)m->W)) return false;
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  size_t o = 0;
+  const size_t hist = o;
+  o += up((size_t)pl->nrange * pl->nbins * 4);
+  const size_t total = o;
+  o += up((size_t)pl->nbins * 4);
+  const size_t base = o;
+  o += up((size_t)(pl->nbins + 1) * 4);
+  const size_t reps = o;
+  o += up((size_t)(n + 63) / 64 * 8);
+  const size_t recs = o;
+  o += up((size_t)(n + 63) / 64 * 16);
+  const size_t range_total = o;
+  o += up((size_t)pl->nrange * 4);
+  const size_t state = o;
+  o += up(sizeof(ash::PartState));
+  const size_t entries = o;
+  o += up((size_t)n * m->slot_words() * 4);
+  const size_t entry_rank = o;
+  o += up((size_t)n * 4);
+  if (m->part_bytes < o) {
+    m->mem.put(m->part, st);
+    m->part_bytes = 0;
+    m->part = (uint8_t*)m->mem.get(o, st);
+    if (!m->part) return false;
+    m->part_bytes = o;
+  }
+  pl->hist = (uint32_t*)(m->part + hist);
+  pl->total = (uint32_t*)(m->part + total);
+  pl->base = (uint32_t*)(m->part + base);
+  pl->reps = (uint64_t*)(m->part + reps);
+  pl->entries = (uint32_t*)(m->part + entries);
+  pr->recs = (uint4*)(m->part + recs);
+  pr->entry_rank = (uint32_t*)(m->part + entry_rank);
+  pr->range_total = (uint32_t*)(m->part + range_total);
+  pr->state = (ash::PartState*)(m->part + state);
+  return true;
+}
+
 ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void* const* values, int32_t* out_idx,
                          uint8_t* out_mask, hipStream_t st, const RequestSource* rs) {
   if (rs) {
@@ -251,9 +326,11 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
   // keys, the claim takes 280 against 379 us with 90% repeats, 497 against
   // 466 us with 50%.  The last finalized insert's new-key fraction (possibly
   // an earlier call's) decides; results do not depend on the choice.
+  bool by_bins = false;
   {
     const volatile Meta* mr = m->mirror_h;
     const uint64_t last_n = mr->last_n, last_new = mr->result;
+    by_bins = !rs && insert_by_bins(m, n, last_n, last_new);
     m->keyed = last_n > 0 && last_new * 10 <= last_n * 4;
     if (m->keyed_override >= 0) m->keyed = m->keyed_override != 0;
   }
@@ -335,9 +412,29 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
       return ASH_OK;
     }
   }
-  ASH_TRY(claim());
-  if (check) ASH_TRY(sum());
-  ASH_TRY(commit(check, 0, out_idx, out_mask));
+  ash::PartPlan pl;
+  ash::PartRanks pr;
+  if (by_bins && part_plan(m, n, &pl, &pr, st)) {
+    // whether the new keys fit is known before anything is stored
+    ASH_HIP(timed(m, "claim_bins", st, [&] {
+      return ash::launch_insert_settle(m->key_dim, pl, pr, m->ref(), keys, m->meta, st);
+    }));
+    uint32_t row_total = 0;
+    for (int j = 0; j < vs.n; ++j) row_total += vs.row_bytes[j];
+    uint32_t* wlist = row_total >= kSplitRowBytes ? reinterpret_cast<uint32_t*>(m->aux) : nullptr;
+    ASH_HIP(timed(m, "commit", st, [&] {
+      return ash::launch_insert_store(m->key_dim, pl, pr, m->ref(), keys, m->kB, m->heap, (uint32_t)m->c, vs, out_idx,
+                                      out_mask, m->meta, wlist, m->slot_of, 0, st);
+    }));
+    if (wlist)
+      ASH_HIP(timed(m, "values", st, [&] {
+        return ash::launch_scatter_values(vs, wlist, m->heap, m->meta, un, (uint32_t)m->c, st);
+      }));
+  } else {
+    ASH_TRY(claim());
+    if (check) ASH_TRY(sum());
+    ASH_TRY(commit(check, 0, out_idx, out_mask));
+  }
   m->live_ub = std::min(m->c, m->live_ub + n);
   m->used_ub += std::min(n, m->c);
   return ASH_OK;
@@ -488,6 +585,7 @@ ash_status_t ash_destroy(ash_map_t m) {
   m->mem.put(m->lost, st);
   m->mem.put(m->scan_status, st);
   m->mem.put(m->batch_dev, st);
+  m->mem.put(m->part, st);
   for (hipEvent_t e : m->prof.pool) (void)hipEventDestroy(e);
   if (m->mirror_h || m->batch_host) {
     (void)hipDeviceSynchronize();  // no finalize may still write the mirror

@@ -66,7 +66,7 @@ struct Meta {
   uint32_t tombs;   // bound on the tombstones; exact after a count
   uint32_t status;  // sticky error bits
   uint32_t epoch;   // tag of the scan status words of the current launch
-  uint32_t spare;
+  uint32_t permuted;  // an erase or a load has reordered the heap since it was 0..c-1 (from t on)
   uint32_t result;  // total of the last scanning kernel
   uint32_t fail;    // groups whose probe found no empty slot (claim/rebuild)
   uint32_t last_n;  // mirror only: batch size of the last finalized insert (its result: new keys)
@@ -148,6 +148,22 @@ struct TableRef {
   uint32_t keyed;         // 1: claims keep pending keys in their slots (no tombstone reuse then)
   Meta* mirror;           // nullable host-mapped copy of the counters, written by every finalize
 };
+
+// Copies the counters a host reader tracks to the table's mirror, if any
+// (vector stores to host-mapped memory, visible once the kernel is done):
+// t and the slot counts, and after an insert of n positions its new-key
+// count, which the host uses to choose the next insert's claim variant.
+__device__ __forceinline__ void publish_counts(const TableRef& tb, const Meta* m, uint32_t insert_n = 0) {
+  if (!tb.mirror) return;
+  tb.mirror->t = m->t;
+  tb.mirror->used = m->used;
+  tb.mirror->tombs = m->tombs;
+  if (insert_n) {
+    tb.mirror->result = m->result;
+    tb.mirror->last_n = insert_n;
+  }
+  __threadfence_system();
+}
 
 // ---------------------------------------------------------------------------
 // Hashing.  The paper leaves the hash function open.  Words are folded with
@@ -484,7 +500,8 @@ __device__ inline void copy_rows(const ValueSet& vs, int j, const uint2* pairs, 
 // ---------------------------------------------------------------------------
 // Batches split by key hash (ash_partition.hip).  n positions in nrange ranges
 // of `per`; nbins bins of whole home buckets (bin = home bucket >> shift).
-constexpr uint32_t kPartTile = 4096;     // positions whose copies are dropped together
+constexpr uint32_t kPartTileLog2 = 12;
+constexpr uint32_t kPartTile = 1u << kPartTileLog2;  // positions whose copies are dropped together
 constexpr uint32_t kPartRanges = 256;    // most ranges
 constexpr uint32_t kPartBins = 4096;     // most bins
 constexpr uint32_t kVoxelBinMean = 3840; // most points per bin of a voxelization, on average
@@ -501,6 +518,25 @@ struct PartPlan {
   uint32_t* base;      // [nbins + 1]: first entry of each bin
   uint64_t* reps;      // a bit per position: it has an entry
   uint32_t* entries;
+};
+
+constexpr uint32_t kPartLost = 0x80000000u;      // an entry's position word: not a new key
+constexpr uint32_t kPartMostPer = 65536;         // most positions per range of an insert by bins
+constexpr uint32_t kPartMostRegion = 1u << 16;   // most table slots per bin (17 bits of LDS each)
+constexpr uint32_t kInsertBinMean = 8192;        // most positions per bin of an insert, on average
+
+// The counters an insert by bins started from, and its spilled keys.
+struct PartState {
+  uint32_t t, used, permuted, spilled;
+};
+
+// The new keys of a batch by position: per 64 positions (bits 0-31, bits
+// 32-63, set bits before them in the range), and each range's number.
+struct PartRanks {
+  uint4* recs;
+  uint32_t* entry_rank;  // per entry: (range << 16) + rank in the range, or kNoSlot
+  uint32_t* range_total;
+  PartState* state;
 };
 
 // ---------------------------------------------------------------------------

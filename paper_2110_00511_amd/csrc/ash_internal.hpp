@@ -170,6 +170,8 @@ struct ash_map {
   int64_t scratch_n = 0;
   uint64_t* scan_status = nullptr;
   int64_t scan_tiles = 0;
+  uint8_t* part = nullptr;      // workspace of the inserts that go by hash bins
+  size_t part_bytes = 0;
   // host-side upper bounds (exact after any synchronizing call)
   int64_t live_ub = 0;
   int64_t used_ub = 0;

@@ -213,6 +213,7 @@ ash_status_t ash_load(const char* path, const ash_allocator_t* allocator, const 
   if (rc == ASH_OK) rc = read_meta(m, &h, st);  // also waits for the uploads above (host vectors stay valid)
   if (rc == ASH_OK) {
     h.t = (uint32_t)t;
+    h.permuted = 1;
     if (hipMemcpyAsync(m->meta, &h, sizeof(Meta), hipMemcpyHostToDevice, st) != hipSuccess) rc = ASH_E_DEVICE;
   }
   if (rc == ASH_OK && t > 0) {

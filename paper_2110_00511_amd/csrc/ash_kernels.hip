@@ -155,6 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_iota(int32_t* __restrict__ h, uint32
 
 __device__ __forceinline__ void reset_meta(Meta* m) {
   m->t = 0; m->claims = 0; m->used = 0; m->tombs = 0; m->status = 0; m->result = 0; m->fail = 0;
+  m->permuted = 0;
   m->epoch = m->epoch + 1u == 0u ? 1u : m->epoch + 1u;
 }
 
@@ -618,6 +619,7 @@ __device__ __forceinline__ void finalize_total(Meta* m, uint32_t cap, int mode, 
     m->fail = 0;
   } else if (mode == kFinalizeErase) {
     m->t -= total;
+    m->permuted = 1;
     m->tombs += total;
     m->result = total;
   } else if (mode == kFinalizeCount) {
@@ -628,22 +630,6 @@ __device__ __forceinline__ void finalize_total(Meta* m, uint32_t cap, int mode, 
     m->fail = 0;
   }
   m->epoch = m->epoch + 1u == 0u ? 1u : m->epoch + 1u;
-}
-
-// Copies the counters a host reader tracks to the table's mirror, if any
-// (vector stores to host-mapped memory, visible once the kernel is done):
-// t and the slot counts, and after an insert of n positions its new-key
-// count, which the host uses to choose the next insert's claim variant.
-__device__ __forceinline__ void publish_counts(const TableRef& tb, const Meta* m, uint32_t insert_n = 0) {
-  if (!tb.mirror) return;
-  tb.mirror->t = m->t;
-  tb.mirror->used = m->used;
-  tb.mirror->tombs = m->tombs;
-  if (insert_n) {
-    tb.mirror->result = m->result;
-    tb.mirror->last_n = insert_n;
-  }
-  __threadfence_system();
 }
 
 __device__ __forceinline__ void finalize_map(Meta* m, uint32_t cap, int mode, int silent, int check,

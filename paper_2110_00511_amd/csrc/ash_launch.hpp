@@ -114,6 +114,18 @@ hipError_t launch_voxel_commit(const TableRef& tb, const float* pts, float voxel
 // The ranges of a batch of n positions split by key hash (n, nrange, per and
 // pos_bits of the plan); false when positions do not fit 30 bits.
 bool part_ranges(PartPlan* pl, uint32_t n);
+// An insert by hash bins, in two steps, both on a plan with ranges of at most
+// kPartMostPer positions and bins of whole buckets (part_buckets; false when
+// the table is too large for the batch).  settle finds the new keys (pr, and
+// marks in the entries); store writes everything: indices, masks, k^B, rows
+// (or wlist, as launch_commit), the table and t.  spill is n uint32 of scratch.
+bool part_buckets(PartPlan* pl, uint32_t nbuckets, uint32_t bucket_width);
+hipError_t launch_insert_settle(int kd, const PartPlan& pl, const PartRanks& pr, const TableRef& tb,
+                                const int32_t* keys, Meta* meta, hipStream_t st);
+hipError_t launch_insert_store(int kd, const PartPlan& pl, const PartRanks& pr, const TableRef& tb,
+                               const int32_t* keys, int32_t* kB, const int32_t* heap, uint32_t cap, const ValueSet& vs,
+                               int32_t* out_idx, uint8_t* out_mask, Meta* meta, uint32_t* wlist, uint32_t* spill,
+                               int silent, hipStream_t st);
 // A whole voxelization by hash bins: the plan's n / nbins must be at most
 // 2 * kVoxelBinMean; link is n words, status a word pair per 1024 points (both
 // need no initial state).  Writes what launch_voxel_commit and
