@@ -66,7 +66,8 @@ ash_status_t ensure_scratch(ash_map* m, int64_t n, hipStream_t st) {
     const size_t lost_bytes = ((size_t)n + 3) / 4 * 4;
     m->slot_of = (uint32_t*)m->mem.get((size_t)n * 4, st);
     m->aux = (int32_t*)m->mem.get((size_t)n * 4, st);
-    m->partial = (uint32_t*)m->mem.get(((size_t)n / 256 + 2) * 4, st);
+    // (a small batch's claim is spread over up to 2048 blocks, see claim_blocks)
+    m->partial = (uint32_t*)m->mem.get((std::max<size_t>((size_t)n / 256, 2048) + 2) * 4, st);
     m->lost = (uint8_t*)m->mem.get(lost_bytes, st);
     if (!m->slot_of || !m->aux || !m->partial || !m->lost) {
       m->scratch_n = 0;
@@ -335,7 +336,7 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
     if (m->keyed_override >= 0) m->keyed = m->keyed_override != 0;
   }
   const uint32_t un = (uint32_t)n;
-  const uint32_t blocks = ash::claim_blocks(m->G, un);
+  const uint32_t blocks = ash::claim_blocks(m->G, un, (m->flags & ASH_F_LDS_DEDUP) != 0);
   auto claim = [&]() -> ash_status_t {
     // the profile names the claim variant that ran (results are the same)
     const char* label = m->tombs_possible ? "claim_reuse" : (m->keyed ? "claim_keyed" : "claim");
@@ -884,7 +885,7 @@ ash_status_t voxel_work(int64_t n, VoxelWork* w) {
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   w->tiles = (n + ash::kScanTile - 1) / ash::kScanTile;
   w->lost_bytes = ((size_t)n + 3) / 4 * 4;
-  const uint32_t blocks = ash::claim_blocks(kVoxG, (uint32_t)n);
+  const uint32_t blocks = ash::claim_blocks(kVoxG, (uint32_t)n, true);
   size_t o = 0;
   w->table = o;
   o += up((size_t)w->nslots * 16);

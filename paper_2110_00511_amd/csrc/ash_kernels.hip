@@ -2000,18 +2000,33 @@ hipError_t launch_sum_partials(const uint32_t* partial, uint32_t count, Meta* me
   return hipGetLastError();
 }
 
-// Positions per block of the probing kernels: 256 (G lanes per position, so
-// a group takes G positions in turn).
-template <int G>
-static inline uint32_t rounds_for() { return 256u / (kBlock / G); }
+// Positions per group and block of the probing kernels on n positions.  G lanes
+// take a position together, so a block of 256 threads has 256 / G groups, and a
+// full tile of 256 positions keeps each group busy for G positions in turn: G
+// chains of dependent loads one after another.  That is right for large
+// batches (one block per 256 positions) and only latency for small ones, so a
+// batch of few tiles is spread until there are about 1024 blocks.
+constexpr uint32_t kSpreadBlocks = 1024;
 
-uint32_t claim_blocks(int g, uint32_t n) { return cdiv(n, 256u); }
+static inline uint32_t rounds_of(uint32_t g, uint32_t n) {
+  const uint32_t groups = kBlock / g;
+  return std::max(1u, std::min(256u / groups, n / (groups * kSpreadBlocks)));
+}
+
+template <int G>
+static inline uint32_t rounds_for(uint32_t n) { return rounds_of(G, n); }
+
+uint32_t claim_blocks(int g, uint32_t n, bool dedup) {
+  // (dropping copies in LDS works on whole tiles of 256)
+  const uint32_t groups = kBlock / (uint32_t)g;
+  return cdiv(n, groups * (dedup ? 256u / groups : rounds_of((uint32_t)g, n)));
+}
 
 template <int KD, int G, int WL>
 struct ClaimK {
   static hipError_t run(const TableRef& tb, const int32_t* keys, uint32_t n, uint32_t* slot_of, uint8_t* lost,
                         uint32_t* partial, Meta* meta, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = tb.dedup ? rounds_for_dev<G>() : rounds_for<G>(n);
     const dim3 grid(cdiv(n, (kBlock / G) * rounds));
     // tombstones are reused only where an erase may have left some
     if (tb.reuse)
@@ -2031,7 +2046,7 @@ template <int KD, int G, int WL>
 struct ClaimRequestsK {
   static hipError_t run(const TableRef& tb, const ReqArgs& args, const ReqDesc* d, int nreq, uint32_t n,
                         uint32_t* slot_of, uint8_t* lost, uint32_t* partial, Meta* meta, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(n);
     const dim3 grid(cdiv(n, (kBlock / G) * rounds));
     if (tb.reuse)
       hipLaunchKernelGGL((k_claim_requests<KD, G, WL, true, false>), grid, dim3(kBlock), 0, st, tb, args, d, nreq, n,
@@ -2051,7 +2066,7 @@ struct EraseMarkRequestsK {
   static hipError_t run(const TableRef& tb, const ReqArgs& args, const ReqDesc* d, int nreq, uint32_t n,
                         uint32_t epoch, uint32_t* slot_of, int32_t* found, uint64_t* owner, uint8_t* lost,
                         hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(n);
     hipLaunchKernelGGL((k_erase_mark_requests<KD, G, WL>), dim3(cdiv(n, (kBlock / G) * rounds)), dim3(kBlock), 0, st,
                        tb, args, d, nreq, n, rounds, epoch, slot_of, found, owner, lost);
     return hipGetLastError();
@@ -2062,7 +2077,7 @@ template <int KD, int G, int WL>
 struct FindK {
   static hipError_t run(const TableRef& tb, const int32_t* keys, uint32_t n, int32_t* out_idx, uint8_t* out_mask,
                         const ValueSet& vs, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(n);
     hipLaunchKernelGGL((k_find<KD, G, WL>), dim3(cdiv(n, (kBlock / G) * rounds)), dim3(kBlock), 0, st, tb, keys, n,
                        rounds, out_idx, out_mask, vs);
     return hipGetLastError();
@@ -2073,7 +2088,7 @@ template <int KD, int G, int WL>
 struct FindRequestsK {
   static hipError_t run(const TableRef& tb, const ReqArgs& args, const ReqDesc* d, int nreq, uint32_t n,
                         const ValueSet& vs, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(n);
     hipLaunchKernelGGL((k_find_requests<KD, G, WL>), dim3(cdiv(n, (kBlock / G) * rounds)), dim3(kBlock), 0, st, tb,
                        args, d, nreq, n, rounds, vs);
     return hipGetLastError();
@@ -2084,7 +2099,7 @@ template <int KD, int G, int WL>
 struct FindOffsetsK {
   static hipError_t run(const TableRef& tb, const int32_t* keys, const int32_t* offsets, uint32_t k, uint32_t n,
                         int32_t* out_idx, uint8_t* out_mask, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(n);
     hipLaunchKernelGGL((k_find_offsets<KD, G, WL>), dim3(cdiv(n, (kBlock / G) * rounds)), dim3(kBlock), 0, st, tb,
                        OffsetKeys<KD>{keys, offsets, k}, n, rounds, out_idx, out_mask);
     return hipGetLastError();
@@ -2095,7 +2110,7 @@ template <int KD, int G, int WL>
 struct EraseMarkK {
   static hipError_t run(const TableRef& tb, const int32_t* keys, uint32_t n, uint32_t epoch, uint32_t* slot_of,
                         int32_t* found, uint64_t* owner, uint8_t* lost, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(n);
     hipLaunchKernelGGL((k_erase_mark<KD, G, WL>), dim3(cdiv(n, (kBlock / G) * rounds)), dim3(kBlock), 0, st, tb,
                        keys, n, rounds, epoch, slot_of, found, owner, lost);
     return hipGetLastError();
@@ -2106,7 +2121,7 @@ template <int KD, int G, int WL>
 struct RebuildK {
   static hipError_t run(const TableRef& tb, const uint32_t* old_words, uint32_t old_slots, Meta* meta,
                         hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for<G>(old_slots);
     hipLaunchKernelGGL((k_rebuild<KD, G, WL>), dim3(cdiv(old_slots, (kBlock / G) * rounds)), dim3(kBlock), 0, st,
                        tb, old_words, old_slots, rounds, meta);
     return hipGetLastError();
@@ -2117,7 +2132,7 @@ template <int KD, int G, int WL>
 struct VoxelClaimK {
   static hipError_t run(const TableRef& tb, const float* pts, float voxel, uint32_t n, uint32_t* slot_of,
                         uint8_t* lost, uint32_t* partial, Meta* meta, hipStream_t st) {
-    const uint32_t rounds = rounds_for<G>();
+    const uint32_t rounds = rounds_for_dev<G>();
     hipLaunchKernelGGL((k_claim<3, G, WL, VoxelKeys, true, false, true>), dim3(cdiv(n, (kBlock / G) * rounds)), dim3(kBlock), 0,
                        st, tb, VoxelKeys{pts, voxel}, n, rounds, slot_of, lost, partial, meta);
     return hipGetLastError();

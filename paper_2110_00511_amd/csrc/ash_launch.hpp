@@ -64,7 +64,8 @@ hipError_t launch_finalize(Meta* m, uint32_t cap, int mode, int silent, int chec
                            uint32_t last_tile, hipStream_t st);
 hipError_t launch_sum_partials(const uint32_t* partial, uint32_t count, Meta* meta, hipStream_t st);
 // Number of blocks (and per-block counts) of a claim launch over n positions.
-uint32_t claim_blocks(int g, uint32_t n);
+// (dedup: TableRef::dedup of the launch).
+uint32_t claim_blocks(int g, uint32_t n, bool dedup);
 hipError_t launch_claim(int kd, int g, int w, const TableRef& tb, const int32_t* keys, uint32_t n, uint32_t* slot_of,
                         uint8_t* lost, uint32_t* partial, Meta* meta, hipStream_t st);
 // The commit's last tile also finalizes the insert (t, counters, epoch;
