@@ -42,8 +42,8 @@
  *     untouched.
  *   - A batch whose new keys exceed the free indices c - t is detected on the
  *     device: nothing is inserted (size, heap, index-addressed buffers and
- *     every stored key are as before; slots the batch had claimed become
- *     tombstones, which later inserts reuse), outputs are idx -1 /
+ *     every stored key are as before; slots the batch had claimed, if any,
+ *     become tombstones, which later inserts reuse), outputs are idx -1 /
  *     mask 0, and ash_device_status() reports ASH_E_CAPACITY.  With
  *     ASH_F_AUTOGROW the map instead grows to the smallest c * 2^k that fits
  *     (this path synchronizes).

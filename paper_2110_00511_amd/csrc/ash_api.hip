@@ -415,7 +415,19 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
   }
   ash::PartPlan pl;
   ash::PartRanks pr;
-  if (by_bins && part_plan(m, n, &pl, &pr, st)) {
+  if (!rs && n <= (int64_t)ash::kSmallBatch) {
+    uint32_t row_total = 0;
+    for (int j = 0; j < vs.n; ++j) row_total += vs.row_bytes[j];
+    uint32_t* wlist = row_total >= kSplitRowBytes ? reinterpret_cast<uint32_t*>(m->aux) : nullptr;
+    ASH_HIP(timed(m, "insert_small", st, [&] {
+      return ash::launch_insert_small(m->key_dim, m->ref(), keys, un, m->kB, m->heap, (uint32_t)m->c, vs, out_idx,
+                                      out_mask, m->meta, wlist, st);
+    }));
+    if (wlist)
+      ASH_HIP(timed(m, "values", st, [&] {
+        return ash::launch_scatter_values(vs, wlist, m->heap, m->meta, un, (uint32_t)m->c, st);
+      }));
+  } else if (by_bins && part_plan(m, n, &pl, &pr, st)) {
     // whether the new keys fit is known before anything is stored
     ASH_HIP(timed(m, "claim_bins", st, [&] {
       return ash::launch_insert_settle(m->key_dim, pl, pr, m->ref(), keys, m->meta, st);
@@ -461,6 +473,13 @@ ash_status_t erase_impl(ash_map* m, const int32_t* keys, int64_t n, uint8_t* out
   if (n == 0) return ASH_OK;
   ASH_TRY(ensure_scratch(m, n, st));
   const uint32_t un = (uint32_t)n;
+  if (!rs && n <= (int64_t)ash::kSmallBatch) {
+    m->tombs_possible = true;
+    ASH_HIP(timed(m, "erase_small", st, [&] {
+      return ash::launch_erase_small(m->key_dim, m->ref(), keys, un, m->heap, out_mask, m->meta, st);
+    }));
+    return ASH_OK;
+  }
   if (++m->erase_epoch == 0) {  // epochs wrapped: start the owner entries afresh
     ASH_HIP(ash::launch_fill_u32((uint32_t*)m->owner, 0u, (size_t)m->c * 2, st));
     m->erase_epoch = 1;

@@ -509,6 +509,8 @@ constexpr uint32_t kVoxelBinMean = 3840; // most points per bin of a voxelizatio
 constexpr uint32_t kVoxelWinner = 0x80000000u;  // + the voxel's count: the first point of its voxel
 constexpr uint32_t kVoxelLocal = 0x40000000u;   // + the position of the range's point it repeats
 
+constexpr uint32_t kSmallBatch = 2048;  // most positions of a batch that one block works on (ash_small.hip)
+
 struct PartPlan {
   uint32_t n, nrange, per, nbins;
   uint32_t nbuckets, shift;

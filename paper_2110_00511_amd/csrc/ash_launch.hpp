@@ -112,6 +112,13 @@ hipError_t launch_voxel_claim(int g, int w, const TableRef& tb, const float* pts
 hipError_t launch_voxel_commit(const TableRef& tb, const float* pts, float voxel, uint32_t n, uint32_t* slot_of,
                                uint8_t* lost, int32_t* voxel_keys, int32_t* counts, int32_t* point_voxel, Meta* meta,
                                uint64_t* status, hipStream_t st);
+// An insert or activate, and an erase, of at most kSmallBatch positions in one
+// block; wlist as for launch_commit (launch_scatter_values must follow then).
+hipError_t launch_insert_small(int kd, const TableRef& tb, const int32_t* keys, uint32_t n, int32_t* kB,
+                               const int32_t* heap, uint32_t cap, const ValueSet& vs, int32_t* out_idx,
+                               uint8_t* out_mask, Meta* meta, uint32_t* wlist, hipStream_t st);
+hipError_t launch_erase_small(int kd, const TableRef& tb, const int32_t* keys, uint32_t n, int32_t* heap,
+                              uint8_t* out_mask, Meta* meta, hipStream_t st);
 // The ranges of a batch of n positions split by key hash (n, nrange, per and
 // pos_bits of the plan); false when positions do not fit 30 bits.
 bool part_ranges(PartPlan* pl, uint32_t n);
