@@ -174,8 +174,11 @@ class TorchAllocator:
     def _do_alloc(self, ctx, nbytes, stream):
         # allocate on the stream the library will use the block on, so that
         # torch only reuses it in that stream's order
-        with torch.cuda.stream(self._stream(stream)):
+        if self.device.index is not None and (stream or 0) == torch._C._cuda_getCurrentRawStream(self.device.index):
             t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+        else:
+            with torch.cuda.stream(self._stream(stream)):
+                t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
         ptr = t.data_ptr()
         self.blocks[ptr] = t
         return ptr

@@ -39,21 +39,32 @@ _DTYPES = {
 }
 
 
+# A call's host time is most of a small batch's (about 10 us of Python against a
+# kernel of 5 to 15 us), so the arguments are made with as few steps as
+# their checks allow, and masks are written as torch.bool in place: the kernels
+# store the bytes 0 and 1.
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-
-
-def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    """The current stream's handle on the current device."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _keys(keys, key_dim, device):
     if not (keys.is_cuda and keys.dtype == torch.int32):
         raise TypeError("keys must be an int32 tensor on the GPU")
-    keys = keys.reshape(-1, key_dim)
-    if not keys.is_contiguous():
-        keys = keys.contiguous()
-    return keys
+    if keys.dim() != 2 or keys.shape[1] != key_dim:
+        keys = keys.reshape(-1, key_dim)
+    return keys if keys.is_contiguous() else keys.contiguous()
+
+
+def _rows(v, n, elems):
+    if v.dim() != 2 or v.shape[0] != n or v.shape[1] != elems:
+        v = v.reshape(n, elems)
+    return v if v.is_contiguous() else v.contiguous()
+
+
+def _pointers(tensors):
+    """A host array of the tensors' device pointers, or None for none."""
+    return (ctypes.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors]) if tensors else None
 
 
 class HashMap:
@@ -65,6 +76,7 @@ class HashMap:
     def __init__(self, capacity, key_dim=3, value_specs=(), device="cuda", bucket_width=4, probe_group=4,
                  max_load=0.5, autogrow=False, lds_dedup=False):
         self._lib = L.load()
+        torch.cuda.init()
         self.device = torch.device(device)
         if self.device.index is None:
             self.device = torch.device("cuda", torch.cuda.current_device())
@@ -94,6 +106,7 @@ class HashMap:
         indices, heap and rows), with the given table tuning."""
         self = cls.__new__(cls)
         self._lib = L.load()
+        torch.cuda.init()
         self.device = torch.device(device)
         if self.device.index is None:
             self.device = torch.device("cuda", torch.cuda.current_device())
@@ -127,6 +140,10 @@ class HashMap:
         self.close()
 
     # -- operations ---------------------------------------------------------
+    def _results(self, n):
+        return (torch.empty(n, dtype=torch.int32, device=self.device),
+                torch.empty(n, dtype=torch.bool, device=self.device))
+
     def insert(self, keys, values=()):
         keys = _keys(keys, self.key_dim, self.device)
         n = keys.shape[0]
@@ -136,42 +153,38 @@ class HashMap:
         for v, (dt, e) in zip(values, self.value_specs):
             if v.dtype != dt or not v.is_cuda:
                 raise TypeError(f"value tensor must be {dt} on the GPU")
-            vals.append(v.reshape(n, e).contiguous())
-        idx = torch.empty(n, dtype=torch.int32, device=self.device)
-        mask = torch.empty(n, dtype=torch.uint8, device=self.device)
-        arr = (ctypes.c_void_p * max(len(vals), 1))(*[v.data_ptr() for v in vals])
-        L.check(self._lib.ash_insert(self._m, _ptr(keys), n, ctypes.cast(arr, ctypes.c_void_p) if vals else None,
-                                     _ptr(idx), _ptr(mask), _stream()), "ash_insert")
-        return idx, mask.bool()
+            vals.append(_rows(v, n, e))
+        idx, mask = self._results(n)
+        L.check(self._lib.ash_insert(self._m, keys.data_ptr(), n, _pointers(vals), idx.data_ptr(), mask.data_ptr(),
+                                     _stream()), "ash_insert")
+        return idx, mask
 
     def activate(self, keys):
         keys = _keys(keys, self.key_dim, self.device)
         n = keys.shape[0]
-        idx = torch.empty(n, dtype=torch.int32, device=self.device)
-        mask = torch.empty(n, dtype=torch.uint8, device=self.device)
-        L.check(self._lib.ash_activate(self._m, _ptr(keys), n, _ptr(idx), _ptr(mask), _stream()), "ash_activate")
-        return idx, mask.bool()
+        idx, mask = self._results(n)
+        L.check(self._lib.ash_activate(self._m, keys.data_ptr(), n, idx.data_ptr(), mask.data_ptr(), _stream()),
+                "ash_activate")
+        return idx, mask
 
     def find(self, keys, gather=False, out_values=None):
         keys = _keys(keys, self.key_dim, self.device)
         n = keys.shape[0]
-        idx = torch.empty(n, dtype=torch.int32, device=self.device)
-        mask = torch.empty(n, dtype=torch.uint8, device=self.device)
+        idx, mask = self._results(n)
         outs = None
         if gather:
             outs = out_values if out_values is not None else [
                 torch.zeros((n, e), dtype=dt, device=self.device) for dt, e in self.value_specs]
-        arr = (ctypes.c_void_p * max(len(outs or []), 1))(*[o.data_ptr() for o in (outs or [])])
-        L.check(self._lib.ash_find(self._m, _ptr(keys), n, _ptr(idx), _ptr(mask),
-                                   ctypes.cast(arr, ctypes.c_void_p) if outs else None, _stream()), "ash_find")
-        return (idx, mask.bool(), outs) if gather else (idx, mask.bool())
+        L.check(self._lib.ash_find(self._m, keys.data_ptr(), n, idx.data_ptr(), mask.data_ptr(),
+                                   _pointers(outs), _stream()), "ash_find")
+        return (idx, mask, outs) if gather else (idx, mask)
 
     def erase(self, keys):
         keys = _keys(keys, self.key_dim, self.device)
         n = keys.shape[0]
-        mask = torch.empty(n, dtype=torch.uint8, device=self.device)
-        L.check(self._lib.ash_erase(self._m, _ptr(keys), n, _ptr(mask), _stream()), "ash_erase")
-        return mask.bool()
+        mask = torch.empty(n, dtype=torch.bool, device=self.device)
+        L.check(self._lib.ash_erase(self._m, keys.data_ptr(), n, mask.data_ptr(), _stream()), "ash_erase")
+        return mask
 
     def find_offsets(self, keys, offsets):
         """Neighbor lookups: finds of keys[q] + offsets[o] (int32, wrapping),
@@ -179,11 +192,10 @@ class HashMap:
         keys = _keys(keys, self.key_dim, self.device)
         offsets = _keys(offsets, self.key_dim, self.device)
         n, k = keys.shape[0], offsets.shape[0]
-        idx = torch.empty((n, k), dtype=torch.int32, device=self.device)
-        mask = torch.empty((n, k), dtype=torch.uint8, device=self.device)
-        L.check(self._lib.ash_find_offsets(self._m, _ptr(keys), n, _ptr(offsets), k, _ptr(idx), _ptr(mask),
-                                           _stream()), "ash_find_offsets")
-        return idx, mask.bool()
+        idx, mask = self._results((n, k))
+        L.check(self._lib.ash_find_offsets(self._m, keys.data_ptr(), n, offsets.data_ptr(), k, idx.data_ptr(),
+                                           mask.data_ptr(), _stream()), "ash_find_offsets")
+        return idx, mask
 
     def intersect(self, keys):
         """The rows of keys that the map holds, in order, duplicates kept
@@ -192,14 +204,15 @@ class HashMap:
         n = keys.shape[0]
         out = torch.empty((max(n, 1), self.key_dim), dtype=torch.int32, device=self.device)
         cnt = ctypes.c_int64()
-        L.check(self._lib.ash_intersect(self._m, _ptr(keys), n, _ptr(out), ctypes.byref(cnt), _stream()),
+        L.check(self._lib.ash_intersect(self._m, keys.data_ptr(), n, out.data_ptr(), ctypes.byref(cnt), _stream()),
                 "ash_intersect")
         return out[: cnt.value]
 
     def active_indices(self):
         out = torch.empty(max(self.capacity, 1), dtype=torch.int32, device=self.device)
         cnt = ctypes.c_int64()
-        L.check(self._lib.ash_active_indices(self._m, _ptr(out), ctypes.byref(cnt), _stream()), "ash_active_indices")
+        L.check(self._lib.ash_active_indices(self._m, out.data_ptr(), ctypes.byref(cnt), _stream()),
+                "ash_active_indices")
         return out[: cnt.value]
 
     def rehash(self, new_capacity):
@@ -301,11 +314,11 @@ def block_coords(points, voxel_size, block_res):
     n = pts.shape[0]
     bk = torch.empty((n, 3), dtype=torch.int32, device=pts.device)
     lc = torch.empty((n, 3), dtype=torch.int32, device=pts.device)
-    ok = torch.empty(n, dtype=torch.uint8, device=pts.device)
+    ok = torch.empty(n, dtype=torch.bool, device=pts.device)
     lib = L.load()
-    L.check(lib.ash_block_coords(_ptr(pts), n, ctypes.c_float(voxel_size), int(block_res), _ptr(bk), _ptr(lc),
-                                 _ptr(ok), _stream()), "ash_block_coords")
-    return bk, lc, ok.bool()
+    L.check(lib.ash_block_coords(pts.data_ptr(), n, ctypes.c_float(voxel_size), int(block_res), bk.data_ptr(),
+                                 lc.data_ptr(), ok.data_ptr(), _stream()), "ash_block_coords")
+    return bk, lc, ok
 
 
 def voxelize(points, voxel_size):
@@ -323,8 +336,8 @@ def voxelize(points, voxel_size):
     cnt = torch.empty(max(n, 1), dtype=torch.int32, device=dev)
     nv = ctypes.c_int64()
     alloc = L.TorchAllocator(dev)
-    L.check(lib.ash_voxelize(_ptr(pts), n, ctypes.c_float(float(voxel_size)), _ptr(pv), _ptr(vk), _ptr(cnt),
-                             ctypes.byref(nv), ctypes.byref(alloc.struct), _stream()), "ash_voxelize")
+    L.check(lib.ash_voxelize(pts.data_ptr(), n, ctypes.c_float(float(voxel_size)), pv.data_ptr(), vk.data_ptr(),
+                             cnt.data_ptr(), ctypes.byref(nv), ctypes.byref(alloc.struct), _stream()), "ash_voxelize")
     u = nv.value
     return pv, vk[:u], cnt[:u]
 
@@ -338,6 +351,7 @@ def autotune(capacity, n_insert, distinct_ratio, key_dim=3, value_specs=(), devi
     that grid instead of the library's default one.  Returns
     (dict(bucket_width, probe_group, max_load), milliseconds)."""
     lib = L.load()
+    torch.cuda.init()
     specs = [(dt, int(e)) for dt, e in value_specs]
     n = len(specs)
     dts = (ctypes.c_int * max(n, 1))(*[_DTYPES[dt] for dt, _ in specs])
@@ -372,34 +386,39 @@ def batched(ops, fused=True):
     lib = L.load()
     arr = (L.AshBatchOp * max(len(ops), 1))()
     keep = []
-    results = []
-    for i, op in enumerate(ops):
+    calls = []
+    for op in ops:
         m = op["map"]
         ik = _keys(op["insert_keys"], m.key_dim, m.device)
         fk = _keys(op["find_keys"], m.key_dim, m.device)
-        ni, nf = ik.shape[0], fk.shape[0]
-        vals = [v.reshape(ni, e).contiguous() for v, (dt, e) in zip(op.get("insert_values", ()), m.value_specs)]
+        ni = ik.shape[0]
+        vals = [_rows(v, ni, e) for v, (dt, e) in zip(op.get("insert_values", ()), m.value_specs)]
         if len(vals) != len(m.value_specs):
             raise ValueError("one value tensor per value buffer is required")
-        res = dict(insert_idx=torch.empty(ni, dtype=torch.int32, device=m.device),
-                   insert_mask=torch.empty(ni, dtype=torch.uint8, device=m.device),
-                   find_idx=torch.empty(nf, dtype=torch.int32, device=m.device),
-                   find_mask=torch.empty(nf, dtype=torch.uint8, device=m.device), find_values=None)
-        vin = (ctypes.c_void_p * max(len(vals), 1))(*[v.data_ptr() for v in vals])
-        vout = None
-        if op.get("gather") and m.value_specs:
+        calls.append((m, ik, ni, vals, fk, fk.shape[0]))
+    # the maps' results are parts of one tensor of each kind
+    device = calls[0][0].device if calls else None
+    if all(c[0].device == device for c in calls):
+        sizes = [c[2] for c in calls] + [c[5] for c in calls]
+        idx = list(torch.empty(sum(sizes), dtype=torch.int32, device=device).split(sizes)) if calls else []
+        mask = list(torch.empty(sum(sizes), dtype=torch.bool, device=device).split(sizes)) if calls else []
+    else:
+        sized = [(c[2], c[0].device) for c in calls] + [(c[5], c[0].device) for c in calls]
+        idx = [torch.empty(k, dtype=torch.int32, device=d) for k, d in sized]
+        mask = [torch.empty(k, dtype=torch.bool, device=d) for k, d in sized]
+    results = []
+    for i, (m, ik, ni, vals, fk, nf) in enumerate(calls):
+        j = len(calls) + i
+        res = dict(insert_idx=idx[i], insert_mask=mask[i], find_idx=idx[j], find_mask=mask[j], find_values=None)
+        if ops[i].get("gather") and m.value_specs:
             res["find_values"] = [torch.zeros((nf, e), dtype=dt, device=m.device) for dt, e in m.value_specs]
-            vout = (ctypes.c_void_p * len(m.value_specs))(*[o.data_ptr() for o in res["find_values"]])
-        keep.extend([ik, fk, vals, vin, vout])
-        arr[i] = L.AshBatchOp(m._m, ik.data_ptr(), ni, ctypes.cast(vin, ctypes.c_void_p) if vals else None,
-                              res["insert_idx"].data_ptr(), res["insert_mask"].data_ptr(), fk.data_ptr(), nf,
-                              ctypes.cast(vout, ctypes.c_void_p) if vout is not None else None,
-                              res["find_idx"].data_ptr(), res["find_mask"].data_ptr())
+        vin, vout = _pointers(vals), _pointers(res["find_values"])
+        keep.append((vin, vout))
+        arr[i] = L.AshBatchOp(m._m, ik.data_ptr(), ni, ctypes.addressof(vin) if vin else None,
+                              idx[i].data_ptr(), mask[i].data_ptr(), fk.data_ptr(), nf,
+                              ctypes.addressof(vout) if vout else None, idx[j].data_ptr(), mask[j].data_ptr())
         results.append(res)
     L.check(lib.ash_batched(arr, len(ops), 1 if fused else 0, _stream()), "ash_batched")
-    for r in results:
-        r["insert_mask"] = r["insert_mask"].bool()
-        r["find_mask"] = r["find_mask"].bool()
     return results
 
 
