@@ -149,10 +149,13 @@ struct TableRef {
   Meta* mirror;           // nullable host-mapped copy of the counters, written by every finalize
 };
 
-// Copies the counters a host reader tracks to the table's mirror, if any
-// (vector stores to host-mapped memory, visible once the kernel is done):
-// t and the slot counts, and after an insert of n positions its new-key
-// count, which the host uses to choose the next insert's claim variant.
+// Copies the counters a host reader tracks to the table's mirror, if any: t and
+// the slot counts, and after an insert of n positions its new-key count, which
+// the host uses to choose the next insert's claim variant.  Vector stores to
+// host-mapped memory that the end of the kernel makes visible; a host reader
+// waits for that.  Waiting for them here (a system-scope fence) would hold the
+// launch's last block for a trip over the bus, so the counters are also
+// written last.
 __device__ __forceinline__ void publish_counts(const TableRef& tb, const Meta* m, uint32_t insert_n = 0) {
   if (!tb.mirror) return;
   tb.mirror->t = m->t;
@@ -162,7 +165,6 @@ __device__ __forceinline__ void publish_counts(const TableRef& tb, const Meta* m
     tb.mirror->result = m->result;
     tb.mirror->last_n = insert_n;
   }
-  __threadfence_system();
 }
 
 // ---------------------------------------------------------------------------

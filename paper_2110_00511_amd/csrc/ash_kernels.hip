@@ -785,14 +785,6 @@ __device__ __forceinline__ void commit_tile_src(const TableRef& tb, const Src& s
   uint32_t total;
   block_rank_rows(win, rank, total, lds.scan);
   const uint32_t prefix = block_lookback(status, tile, meta->epoch, total, &meta->status, &lds.prefix);
-  // fin >= 0: the last tile finalizes the insert (fin = silent flag).  Its
-  // look-back saw every other tile publish, and each tile publishes only
-  // after reading t, the epoch and the claim counters, so none reads them
-  // after this point; the next kernel sees the update at the launch boundary.
-  if (fin >= 0 && threadIdx.x == 0 && tile == (n - 1) / kScanTile) {
-    finalize_total(meta, cap, kFinalizeInsert, fin, check, prefix + total, n);
-    publish_counts(tb, meta, n);
-  }
   bool bad = false;
 #pragma unroll
   for (int r = 0; r < kScanItems; ++r) {
@@ -817,6 +809,14 @@ __device__ __forceinline__ void commit_tile_src(const TableRef& tb, const Src& s
     if (vs.n > 0 && !__syncthreads_or(bad)) {
       for (int j = 0; j < vs.n; ++j) rows.copy(vs, j, s_pairs, total);
     }
+  }
+  // fin >= 0: the last tile finalizes the insert (fin = silent flag).  Its
+  // look-back saw every other tile publish, and each tile publishes only
+  // after reading t, the epoch and the claim counters, so none reads them
+  // after this point; the next kernel sees the update at the launch boundary.
+  if (fin >= 0 && threadIdx.x == 0 && tile == (n - 1) / kScanTile) {
+    finalize_total(meta, cap, kFinalizeInsert, fin, check, prefix + total, n);
+    publish_counts(tb, meta, n);
   }
   __syncthreads();  // LDS is reused by the next tile of a persistent block
 }
@@ -1133,12 +1133,6 @@ __device__ __forceinline__ void erase_commit_tile(const TableRef& tb, uint32_t n
   block_rank_rows(win, rank, total, s_scan);
   block_lookback(status, tile, meta->epoch, total, &meta->status, s_prefix);
   const uint32_t prefix = *s_prefix;
-  // the last tile finalizes the erase (every tile read t and the epoch before
-  // publishing, see commit_tile)
-  if (threadIdx.x == 0 && tile == (n - 1) / kScanTile) {
-    finalize_total(meta, 0u, kFinalizeErase, 0, 0, prefix + total);
-    publish_counts(tb, meta);
-  }
 #pragma unroll
   for (int r = 0; r < kScanItems; ++r) {
     const uint32_t p = base + r * kBlock + threadIdx.x;
@@ -1148,6 +1142,12 @@ __device__ __forceinline__ void erase_commit_tile(const TableRef& tb, uint32_t n
       tb.words[(size_t)slot_of[p] * S + S - 1] = kTomb;
     }
     out.put(p, win[r] ? 0u : kNoSlot);
+  }
+  // the last tile finalizes the erase (every tile read t and the epoch before
+  // publishing, see commit_tile)
+  if (threadIdx.x == 0 && tile == (n - 1) / kScanTile) {
+    finalize_total(meta, 0u, kFinalizeErase, 0, 0, prefix + total);
+    publish_counts(tb, meta);
   }
 }
 

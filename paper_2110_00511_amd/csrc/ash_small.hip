@@ -222,18 +222,6 @@ __global__ __launch_bounds__(kThreads) void k_insert_small(TableRef tb, BatchKey
   uint32_t rank[kItems];
   const uint32_t total = small_ranks<KD, kItems>(s, win, rank);
   const bool overflow = table_full || total > cap - t0;
-  if (tid == 0) {
-    if (overflow) {
-      meta->result = 0;
-      __hip_atomic_fetch_or(&meta->status, table_full ? kStatusTableFull : kStatusCapacity, __ATOMIC_RELAXED,
-                            __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      meta->t = t0 + total;
-      meta->used += total;  // a bound: tombstones may be taken
-      meta->result = total;
-    }
-    publish_counts(tb, meta, n);
-  }
 #pragma unroll
   for (uint32_t r = 0; r < kItems; ++r) {
     const uint32_t p = r * kThreads + tid;
@@ -253,9 +241,22 @@ __global__ __launch_bounds__(kThreads) void k_insert_small(TableRef tb, BatchKey
     if (out_mask) out_mask[p] = in ? 1 : 0;
   }
   if constexpr (kInline) {
-    if (vs.n == 0 || overflow) return;
-    __syncthreads();
-    for (int j = 0; j < vs.n; ++j) copy_rows(vs, j, s_pairs, total);
+    if (vs.n > 0 && !overflow) {
+      __syncthreads();
+      for (int j = 0; j < vs.n; ++j) copy_rows(vs, j, s_pairs, total);
+    }
+  }
+  if (tid == 0) {
+    if (overflow) {
+      meta->result = 0;
+      __hip_atomic_fetch_or(&meta->status, table_full ? kStatusTableFull : kStatusCapacity, __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      meta->t = t0 + total;
+      meta->used += total;  // a bound: tombstones may be taken
+      meta->result = total;
+    }
+    publish_counts(tb, meta, n);
   }
 }
 
@@ -285,13 +286,6 @@ __global__ __launch_bounds__(kThreads) void k_erase_small(TableRef tb, BatchKeys
   }
   uint32_t rank[kItems];
   const uint32_t total = small_ranks<KD, kItems>(s, win, rank);
-  if (tid == 0) {
-    meta->t = t0 - total;
-    meta->tombs += total;
-    meta->result = total;
-    meta->permuted = 1;
-    publish_counts(tb, meta);
-  }
 #pragma unroll
   for (uint32_t r = 0; r < kItems; ++r) {
     const uint32_t p = r * kThreads + tid;
@@ -301,6 +295,13 @@ __global__ __launch_bounds__(kThreads) void k_erase_small(TableRef tb, BatchKeys
       tb.words[(size_t)f[r].slot * S + S - 1] = kTomb;
     }
     if (out_mask) out_mask[p] = win[r] ? 1 : 0;
+  }
+  if (tid == 0) {
+    meta->t = t0 - total;
+    meta->tombs += total;
+    meta->result = total;
+    meta->permuted = 1;
+    publish_counts(tb, meta);
   }
 }
 
