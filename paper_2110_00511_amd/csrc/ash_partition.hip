@@ -8,7 +8,7 @@
 // kernels, and everything that needed atomics then happens per bin in the LDS
 // of one block:
 //   count    each block takes a contiguous range of positions, drops the
-//            copies of a key within 2048 positions in LDS (so a key repeated
+//            copies of a key within 4096 positions in LDS (so a key repeated
 //            throughout the batch cannot fill a bin) and counts its remaining
 //            keys per bin;
 //   scan     per bin, the exclusive prefix of the ranges' counts;
@@ -81,7 +81,7 @@ __device__ __forceinline__ uint32_t copies_per_entry(const PartPlan& pl) { retur
 // kVoxelWinner + number of copies for a position that goes to a bin, else
 // kVoxelLocal + the position it repeats, or kNoSlot for a rejected point.
 // Bound by arithmetic (the hash, three divisions for a point) and LDS latency:
-// 48 us at 5M points, whose streams alone take 16.  One block of 16 waves per
+// 35 us at 5M points (50 at 10M keys), whose streams alone take 16.  One block of 16 waves per
 // CU; the next tile's keys are loaded while the current one is worked on.
 template <int KD, typename Src, bool kVoxel>
 __global__ __launch_bounds__(kCountThreads) void k_part_count(Src src, PartPlan pl, uint32_t* __restrict__ link,
@@ -605,7 +605,7 @@ __global__ __launch_bounds__(kBlock) void k_voxel_number(VoxelKeys src, uint32_t
 }
 
 // The other points take their first point's id, through the point of their
-// own 2048 that went to the bin where they were dropped in favor of it.
+// own 4096 that went to the bin where they were dropped in favor of it.
 __global__ __launch_bounds__(kBlock) void k_voxel_follow(uint32_t n, const uint32_t* __restrict__ link,
                                                          int32_t* __restrict__ point_voxel) {
   const uint32_t base = blockIdx.x * kScanTile + threadIdx.x;
