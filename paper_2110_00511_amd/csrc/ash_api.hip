@@ -979,7 +979,7 @@ struct VoxelPartWork {
 // 307,200 108 / 93, 1M 178 / 113, 5M 534 / 297; at 5 mm (nearly every point a
 // voxel) 84 / 86, 88 / 86, 93 / 91, 141 / 107 and 435 / 305.  (Later work on
 // the count and the scatter, and less host work around both paths, brought the
-// bins to 80, 107 and 263 us at 5 cm and 76, 105 and 257 at 5 mm for 307,200,
+// bins to 80, 105 and 264 us at 5 cm and 77, 102 and 247 at 5 mm for 307,200,
 // 1M and 5M points.)
 constexpr int64_t kVoxelPartMin = 1 << 18;
 

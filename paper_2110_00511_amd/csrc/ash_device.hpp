@@ -417,15 +417,16 @@ __device__ __forceinline__ uint32_t block_lookback(uint64_t* status, uint32_t ti
 }
 
 // Exclusive block scan of kScanItems 0/1 flags per thread where the item of
-// thread t in row r is position base + r * kBlock + t.  Returns the rank of
+// thread t in row r is position base + r * kThreads + t.  Returns the rank of
 // each flagged item among the tile's flagged items (in position order) and the
-// tile total.  s_scratch needs kBlock / 64 + 1 uint64 words.
+// tile total.  s_scratch needs kThreads / 64 + 1 uint64 words.
+template <int kThreads = kBlock>
 __device__ inline void block_rank_rows(const bool (&flag)[kScanItems], uint32_t (&rank)[kScanItems],
                                        uint32_t& total, uint64_t* s_scratch) {
   const uint32_t lane = lane_id();
   const uint32_t wave = threadIdx.x >> 6;
-  constexpr int kWaves = kBlock / 64;
-  // four 16-bit counters packed in one 64-bit word (each sum <= kBlock)
+  constexpr int kWaves = kThreads / 64;
+  // four 16-bit counters packed in one 64-bit word (each sum <= kThreads)
   uint64_t v = 0;
 #pragma unroll
   for (int r = 0; r < kScanItems; ++r) v |= (uint64_t)(flag[r] ? 1u : 0u) << (16 * r);
