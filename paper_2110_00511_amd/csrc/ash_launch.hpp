@@ -124,7 +124,7 @@ hipError_t launch_erase_small(int kd, const TableRef& tb, const int32_t* keys, u
 bool part_ranges(PartPlan* pl, uint32_t n);
 // An insert by hash bins, in two steps, both on a plan with ranges of at most
 // kPartMostPer positions and bins of whole buckets (part_buckets; false when
-// the table is too large for the batch).  settle finds the new keys (pr, and
+// the table is too large or too small for the batch).  settle finds the new keys (pr, and
 // marks in the entries); store writes everything: indices, masks, k^B, rows
 // (or wlist, as launch_commit), the table and t.  spill is n uint32 of scratch.
 bool part_buckets(PartPlan* pl, uint32_t nbuckets, uint32_t bucket_width);

@@ -1244,6 +1244,10 @@ bool part_buckets(PartPlan* pl, uint32_t nbuckets, uint32_t bucket_width) {
   const uint64_t mean = std::min<uint64_t>(kInsertBinMean, std::max<uint64_t>(pl->n / 256, 1024));
   while (pl->shift < 31 && (uint64_t)pl->n << (pl->shift + 1) <= mean * nbuckets) ++pl->shift;
   pl->nbins = bins();
+  // a table of few buckets (of a few thousand slots, against at least 2.6M
+  // positions) has no bins that small: entries beyond a bin's LDS table are
+  // settled by a scan of the bin, quadratic in what does not fit it
+  if ((uint64_t)pl->n << pl->shift > (uint64_t)kInsertBinMean * nbuckets) return false;
   // a bin's part of the table has a bit per slot in LDS
   return pl->nbins <= kPartBins && ((uint64_t)bucket_width << pl->shift) <= kPartMostRegion;
 }
