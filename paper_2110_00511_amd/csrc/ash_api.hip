@@ -254,9 +254,22 @@ bool insert_by_bins(const ash_map* m, int64_t n, uint64_t last_n, uint64_t last_
   return last_n == 0 || last_new * 100 > last_n * 35;
 }
 
+// Whether work on st is being captured.  (Asked of the null stream while
+// another stream captures, the runtime answers with an error: that is a yes,
+// since nothing may be allocated then.)
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // The plan and workspace of a batch of n positions by hash bins on m's table;
 // false when it does not fit the plan's limits or its workspace cannot be had
-// (the general path then runs).
+// (the general path then runs).  Which path an insert takes depends on what
+// ran before it, so a batch whose size has run already may be the first one
+// that needs the workspace: under capture, where an allocation would end the
+// capture, the general path runs in its place.
 bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hipStream_t st) {
   if (n > (int64_t)ash::kPartRanges * ash::kPartMostPer) return false;
   std::memset(pl, 0, sizeof(*pl));
@@ -283,6 +296,7 @@ bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hip
   const size_t entry_rank = o;
   o += up((size_t)n * 4);
   if (m->part_bytes < o) {
+    if (capturing(st)) return false;
     m->mem.put(m->part, st);
     m->part_bytes = 0;
     m->part = (uint8_t*)m->mem.get(o, st);
