@@ -295,14 +295,18 @@ bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hip
   o += up((size_t)n * m->slot_words() * 4);
   const size_t entry_rank = o;
   o += up((size_t)n * 4);
+  const bool captured = capturing(st);
   if (m->part_bytes < o) {
-    if (capturing(st)) return false;
-    m->mem.put(m->part, st);
+    if (captured) return false;
+    if (m->part_captured) m->part_kept.push_back(m->part);
+    else m->mem.put(m->part, st);
+    m->part_captured = false;
     m->part_bytes = 0;
     m->part = (uint8_t*)m->mem.get(o, st);
     if (!m->part) return false;
     m->part_bytes = o;
   }
+  m->part_captured = m->part_captured || captured;
   pl->hist = (uint32_t*)(m->part + hist);
   pl->total = (uint32_t*)(m->part + total);
   pl->base = (uint32_t*)(m->part + base);
@@ -620,6 +624,7 @@ ash_status_t ash_destroy(ash_map_t m) {
   m->mem.put(m->scan_status, st);
   m->mem.put(m->batch_dev, st);
   m->mem.put(m->part, st);
+  for (uint8_t* p : m->part_kept) m->mem.put(p, st);
   for (hipEvent_t e : m->prof.pool) (void)hipEventDestroy(e);
   if (m->mirror_h || m->batch_host) {
     (void)hipDeviceSynchronize();  // no finalize may still write the mirror

@@ -172,6 +172,10 @@ struct ash_map {
   int64_t scan_tiles = 0;
   uint8_t* part = nullptr;      // workspace of the inserts that go by hash bins
   size_t part_bytes = 0;
+  // A captured insert works in `part`, so its graph may use the block as long
+  // as the map lives: when it is outgrown it goes to part_kept.
+  bool part_captured = false;
+  std::vector<uint8_t*> part_kept;
   // host-side upper bounds (exact after any synchronizing call)
   int64_t live_ub = 0;
   int64_t used_ub = 0;

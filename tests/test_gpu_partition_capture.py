@@ -74,3 +74,42 @@ def test_a_size_that_has_run_can_be_captured(ash):
     finally:
         torch.cuda.synchronize()
         L.check(lib.ash_destroy(h), "ash_destroy")
+
+
+def test_a_graph_keeps_its_workspace(ash):
+    """A captured insert goes on using its workspace after a larger eager insert
+    has taken one of its own (the map's other scratch is large enough for both
+    from the start, so a graph on it stays valid)."""
+    n, big = INSERT_MIN + 11, 2 * INSERT_MIN
+    m = ash.HashSet(big, 3)
+    m.erase(draw(3, big, 3, 100))  # scratch for the larger batch
+    small, large = draw(4, n, 3, 6 * n), draw(5, big, 3, 6 * big)
+    m.activate(small)
+    m.clear()
+    torch.cuda.synchronize()
+    held = dict(m._alloc.blocks)
+    keys = small.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        idx, mask = m.activate(keys)
+    m.profile()
+    eager = ash.HashSet(big, 3)
+    for seed in (6, 7):
+        m.clear()
+        m.profile_collect()
+        got = m.activate(large)
+        assert "claim_bins" in m.profile_collect()
+        eager.clear()
+        want = in_parts(eager, large)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        gone = [p for p in held if p not in m._alloc.blocks]
+        assert not gone, "a block that the graph may use went back to the allocator"
+        keys.copy_(draw(seed, n, 3, 6 * n))
+        m.clear()
+        graph.replay()
+        eager.clear()
+        want = in_parts(eager, keys)
+        assert torch.equal(idx, want[0]) and torch.equal(mask, want[1])
+        assert m.device_status() == 0
+    m.close()
+    assert not m._alloc.blocks
