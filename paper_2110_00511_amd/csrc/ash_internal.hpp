@@ -75,19 +75,22 @@ struct DevMem {
   bool custom = false;  // hipMalloc / hipFree unless an allocator was given
   // Kernels load 16-byte slots, CAS 8-byte pairs and fill 16 bytes at a
   // time from the start of each block, so a block that is not 256-byte
-  // aligned is handed back and reported as an allocation failure.
+  // aligned is handed back and reported as an allocation failure.  A failure
+  // is the caller's to report or to work around: it leaves no error in the
+  // runtime for the next launch to find.
   void* get(size_t bytes, hipStream_t st) {
     bytes = std::max<size_t>(bytes, 256);
+    void* p = nullptr;
     if (custom) {
-      void* p = a.alloc(a.ctx, bytes, st);
+      p = a.alloc(a.ctx, bytes, st);
       if (p && ((uintptr_t)p & 255u) != 0) {
         a.free(a.ctx, p, st);
-        return nullptr;
+        p = nullptr;
       }
-      return p;
+    } else if (hipMalloc(&p, bytes) != hipSuccess) {
+      p = nullptr;
     }
-    void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (!p) (void)hipGetLastError();
     return p;
   }
   void put(void* p, hipStream_t st) {
