@@ -121,7 +121,16 @@ typedef struct {
  * [0, 2^31 - 3]; key_dim in [1, 4]; n_values in [0, 8]; value_elems[j] > 0.
  * Besides the device buffers from the allocator, the map holds 64 bytes of
  * pinned host memory (hipHostMalloc) that its kernels write the counters
- * to.  Synchronizes `stream` once the buffers are initialised. */
+ * to.  Synchronizes `stream` once the buffers are initialised.
+ * Later calls take from the same allocator, when a call needs more than is
+ * there: scratch for the largest batch so far (9 bytes per position and 8 per
+ * 1024), and for an insert into an empty map that goes by hash bins (from 2.6M
+ * positions on) a workspace of about 12, 20 or 36 bytes per position (key_dim
+ * 1, 2 and 3, 4) and up to 4 MB, kept for the next such insert.  The workspace goes
+ * back when another allocation of the map fails, when the map grows and at
+ * ash_destroy, except that one used under stream capture stays until
+ * ash_destroy.  An insert that cannot have it (also under capture, where
+ * nothing is allocated for it) runs without. */
 ash_status_t ash_create(int64_t capacity, int32_t key_dim, int32_t n_values,
                         const ash_dtype_t* value_dtypes, const int64_t* value_elems,
                         const ash_allocator_t* allocator, const ash_tuning_t* tuning,

@@ -57,6 +57,21 @@ ash_status_t read_meta(ash_map* m, Meta* out, hipStream_t st) {
   return ASH_OK;
 }
 
+// Gives the workspace of the large inserts back, unless a graph may use it.
+bool part_release(ash_map* m, hipStream_t st) {
+  if (!m->part || m->part_captured) return false;
+  m->mem.put(m->part, st);
+  m->part = nullptr;
+  m->part_bytes = 0;
+  return true;
+}
+
+void* map_get(ash_map* m, size_t bytes, hipStream_t st) {
+  void* p = m->mem.get(bytes, st);
+  if (!p && part_release(m, st)) p = m->mem.get(bytes, st);
+  return p;
+}
+
 ash_status_t ensure_scratch(ash_map* m, int64_t n, hipStream_t st) {
   if (n > m->scratch_n) {
     m->mem.put(m->slot_of, st);
@@ -64,11 +79,11 @@ ash_status_t ensure_scratch(ash_map* m, int64_t n, hipStream_t st) {
     m->mem.put(m->partial, st);
     m->mem.put(m->lost, st);
     const size_t lost_bytes = ((size_t)n + 3) / 4 * 4;
-    m->slot_of = (uint32_t*)m->mem.get((size_t)n * 4, st);
-    m->aux = (int32_t*)m->mem.get((size_t)n * 4, st);
+    m->slot_of = (uint32_t*)map_get(m, (size_t)n * 4, st);
+    m->aux = (int32_t*)map_get(m, (size_t)n * 4, st);
     // (a small batch's claim is spread over up to 2048 blocks, see claim_blocks)
-    m->partial = (uint32_t*)m->mem.get((std::max<size_t>((size_t)n / 256, 2048) + 2) * 4, st);
-    m->lost = (uint8_t*)m->mem.get(lost_bytes, st);
+    m->partial = (uint32_t*)map_get(m, (std::max<size_t>((size_t)n / 256, 2048) + 2) * 4, st);
+    m->lost = (uint8_t*)map_get(m, lost_bytes, st);
     if (!m->slot_of || !m->aux || !m->partial || !m->lost) {
       m->scratch_n = 0;
       return ASH_E_NOMEM;
@@ -79,7 +94,7 @@ ash_status_t ensure_scratch(ash_map* m, int64_t n, hipStream_t st) {
   const int64_t tiles = (std::max(n, m->c) + ash::kScanTile - 1) / ash::kScanTile + 1;
   if (tiles > m->scan_tiles) {
     m->mem.put(m->scan_status, st);
-    m->scan_status = (uint64_t*)m->mem.get((size_t)tiles * 8, st);
+    m->scan_status = (uint64_t*)map_get(m, (size_t)tiles * 8, st);
     if (!m->scan_status) {
       m->scan_tiles = 0;
       return ASH_E_NOMEM;
@@ -108,7 +123,7 @@ void free_buffers(ash_map* m, hipStream_t st) {
 ash_status_t rebuild_table(ash_map* m, int64_t live, hipStream_t st, int64_t room_for) {
   uint32_t nslots;
   ASH_TRY(slots_for(std::max(m->c, room_for), m->max_load, m->W, m->G, &nslots));
-  uint32_t* fresh = (uint32_t*)m->mem.get((size_t)nslots * m->slot_words() * 4, st);
+  uint32_t* fresh = (uint32_t*)map_get(m, (size_t)nslots * m->slot_words() * 4, st);
   if (!fresh) return ASH_E_NOMEM;
   ASH_HIP(ash::launch_fill_u32(fresh, ash::kEmpty, (size_t)nslots * m->slot_words(), st));
   uint32_t* old = m->table;
@@ -141,14 +156,15 @@ ash_status_t grow(ash_map* m, int64_t new_c, hipStream_t st) {
   if (new_c != m->c) {
     uint32_t probe_slots;
     ASH_TRY(slots_for(new_c, m->max_load, m->W, m->G, &probe_slots));
+    part_release(m, st);  // old and new buffers are held together from here on
     const int64_t keep = m->c;
-    int32_t* kB = (int32_t*)m->mem.get((size_t)new_c * m->key_dim * 4, st);
-    int32_t* heap = (int32_t*)m->mem.get((size_t)new_c * 4, st);
-    uint64_t* owner = (uint64_t*)m->mem.get((size_t)new_c * 8, st);
+    int32_t* kB = (int32_t*)map_get(m, (size_t)new_c * m->key_dim * 4, st);
+    int32_t* heap = (int32_t*)map_get(m, (size_t)new_c * 4, st);
+    uint64_t* owner = (uint64_t*)map_get(m, (size_t)new_c * 8, st);
     std::vector<uint8_t*> vB(m->n_values, nullptr);
     bool ok = kB && heap && owner;
     for (int j = 0; j < m->n_values && ok; ++j) {
-      vB[j] = (uint8_t*)m->mem.get((size_t)new_c * m->row_bytes[j], st);
+      vB[j] = (uint8_t*)map_get(m, (size_t)new_c * m->row_bytes[j], st);
       ok = vB[j] != nullptr;
     }
     if (!ok) {
@@ -298,8 +314,7 @@ bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hip
   const bool captured = capturing(st);
   if (m->part_bytes < o) {
     if (captured) return false;
-    if (m->part_captured) m->part_kept.push_back(m->part);
-    else m->mem.put(m->part, st);
+    if (!part_release(m, st) && m->part) m->part_kept.push_back(m->part);
     m->part_captured = false;
     m->part_bytes = 0;
     m->part = (uint8_t*)m->mem.get(o, st);
@@ -743,7 +758,7 @@ ash_status_t ash_intersect(ash_map_t m, const int32_t* keys, int64_t n, int32_t*
   }
   hipStream_t st = (hipStream_t)stream;
   ASH_TRY(ensure_scratch(m, n, st));  // look-back status words for n positions
-  uint8_t* mask = (uint8_t*)m->mem.get((size_t)n, st);
+  uint8_t* mask = (uint8_t*)map_get(m, (size_t)n, st);
   if (!mask) return ASH_E_NOMEM;
   ValueSet none;
   std::memset(&none, 0, sizeof(none));
@@ -810,7 +825,7 @@ ash_status_t ash_active_indices(ash_map_t m, int32_t* out_idx, int64_t* out_coun
     return ASH_OK;
   }
   const size_t flag_bytes = ((size_t)m->c + 3) / 4 * 4;
-  uint8_t* flags = (uint8_t*)m->mem.get(flag_bytes, st);
+  uint8_t* flags = (uint8_t*)map_get(m, flag_bytes, st);
   if (!flags) return ASH_E_NOMEM;
   const uint32_t last_tile = (uint32_t)((m->c + ash::kScanTile - 1) / ash::kScanTile - 1);
   ash_status_t rc = ASH_OK;
@@ -1323,7 +1338,7 @@ ash_status_t ash_batched(const ash_batch_op_t* ops, int32_t n_ops, int32_t fused
   if (m0->batch_dev_bytes < bytes) {
     m0->mem.put(m0->batch_dev, st);
     m0->batch_dev_bytes = 0;
-    m0->batch_dev = (uint8_t*)m0->mem.get(bytes, st);
+    m0->batch_dev = (uint8_t*)map_get(m0, bytes, st);
     if (!m0->batch_dev) return ASH_E_NOMEM;
     m0->batch_dev_bytes = bytes;
   }

@@ -173,7 +173,9 @@ struct ash_map {
   int64_t scratch_n = 0;
   uint64_t* scan_status = nullptr;
   int64_t scan_tiles = 0;
-  uint8_t* part = nullptr;      // workspace of the inserts that go by hash bins
+  // Workspace of the inserts that go by hash bins, kept between them (see
+  // map_get and grow for when it goes back).
+  uint8_t* part = nullptr;
   size_t part_bytes = 0;
   // A captured insert works in `part`, so its graph may use the block as long
   // as the map lives: when it is outgrown it goes to part_kept.
@@ -230,6 +232,9 @@ namespace ash_host {
 // Implemented in ash_api.hip.
 ash_status_t read_meta(ash_map* m, Meta* out, hipStream_t st);
 ash_status_t ensure_scratch(ash_map* m, int64_t n, hipStream_t st);
+// A block from the map's allocator.  Where there is none, the workspace of
+// the large inserts, which only makes them faster, goes back first.
+void* map_get(ash_map* m, size_t bytes, hipStream_t st);
 // Rebuilds the slot table from the committed slots of m->table (m->nslots of
 // them), which it frees; live = number of committed slots.  Synchronizes.
 ash_status_t rebuild_table(ash_map* m, int64_t live, hipStream_t st, int64_t room_for = 0);

@@ -69,7 +69,7 @@ ash_status_t ash_save(ash_map_t m, const char* path, void* stream) {
   const int64_t t = h.t;
   std::vector<int32_t> live(std::max<int64_t>(t, 1));
   if (c > 0) {
-    int32_t* d_live = (int32_t*)m->mem.get((size_t)c * 4, st);
+    int32_t* d_live = (int32_t*)map_get(m, (size_t)c * 4, st);
     if (!d_live) return ASH_E_NOMEM;
     int64_t count = 0;
     ash_status_t rc = ash_active_indices(m, d_live, &count, stream);

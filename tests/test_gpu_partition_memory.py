@@ -83,3 +83,46 @@ def test_no_workspace_to_be_had(ash):
     finally:
         L.check(L.load().ash_destroy(h), "ash_destroy")
     assert not budget.blocks
+
+
+def erase(L, h, keys):
+    n = keys.shape[0]
+    mask = torch.empty(n, dtype=torch.uint8, device="cuda")
+    L.check(L.load().ash_erase(h, keys.data_ptr(), n, mask.data_ptr(), stream()), "ash_erase")
+    return mask.cpu().numpy()
+
+
+@pytest.mark.parametrize("call", ["erase", "rehash", "insert"])
+def test_short_of_memory_beside_the_workspace(ash, call):
+    """What fits beside a map without the workspace of its large inserts fits
+    beside one that holds it: it goes back when memory is short."""
+    from paper_2110_00511_amd import _lib as L
+    n = INSERT_MIN + 21
+    rng = np.random.default_rng(2)
+    keys = rng.integers(0, 100, size=(n, 3), dtype=np.int32)
+    budget = Budget(L)
+    h = create(L, n // 2, 3, budget)
+    try:
+        orc = OracleMap(n // 2, 3)
+        got = activate(L, h, torch.from_numpy(keys).cuda())
+        _, idx, mask = orc.activate(keys)
+        assert np.array_equal(got[0], idx) and np.array_equal(got[1], mask)
+        held = max(budget.blocks.values(), key=torch.Tensor.numel).numel()
+        assert held >= 20 * n  # the workspace, the largest block of all
+        budget.most = sum(t.numel() for t in budget.blocks.values()) + n  # nearly all there is
+        more = rng.integers(-50, 90, size=(2 * n, 3), dtype=np.int32)
+        if call == "erase":
+            assert np.array_equal(erase(L, h, torch.from_numpy(more).cuda()), orc.erase(more)[1])
+        elif call == "insert":
+            got = activate(L, h, torch.from_numpy(more).cuda())
+            st, idx, mask = orc.activate(more)
+            assert np.array_equal(got[0], idx) and np.array_equal(got[1], mask)
+        else:
+            L.check(L.load().ash_rehash(h, n // 2 + 1000, stream()), "ash_rehash")
+        assert max(t.numel() for t in budget.blocks.values()) < held
+        size = ctypes.c_int64()
+        L.check(L.load().ash_size(h, ctypes.byref(size), stream()), "ash_size")
+        assert size.value == orc.size
+    finally:
+        L.check(L.load().ash_destroy(h), "ash_destroy")
+    assert not budget.blocks
