@@ -129,8 +129,8 @@ typedef struct {
  * 1, 2 and 3, 4) and up to 4 MB, kept for the next such insert.  The workspace goes
  * back when another allocation of the map fails, when the map grows and at
  * ash_destroy, except that one used under stream capture stays until
- * ash_destroy.  An insert that cannot have it (also under capture, where
- * nothing is allocated for it) runs without. */
+ * ash_destroy.  An insert that cannot have it (also under capture and while the
+ * map is served, where nothing is allocated for it) runs without. */
 ash_status_t ash_create(int64_t capacity, int32_t key_dim, int32_t n_values,
                         const ash_dtype_t* value_dtypes, const int64_t* value_elems,
                         const ash_allocator_t* allocator, const ash_tuning_t* tuning,

@@ -285,7 +285,7 @@ bool capturing(hipStream_t st) {
 // (the general path then runs).  Which path an insert takes depends on what
 // ran before it, so a batch whose size has run already may be the first one
 // that needs the workspace: under capture, where an allocation would end the
-// capture, the general path runs in its place.
+// capture, and on a server's thread, the general path runs in its place.
 bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hipStream_t st) {
   if (n > (int64_t)ash::kPartRanges * ash::kPartMostPer) return false;
   std::memset(pl, 0, sizeof(*pl));
@@ -313,7 +313,7 @@ bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hip
   o += up((size_t)n * 4);
   const bool captured = capturing(st);
   if (m->part_bytes < o) {
-    if (captured) return false;
+    if (captured || m->served) return false;
     if (!part_release(m, st) && m->part) m->part_kept.push_back(m->part);
     m->part_captured = false;
     m->part_bytes = 0;

@@ -181,6 +181,9 @@ struct ash_map {
   // as the map lives: when it is outgrown it goes to part_kept.
   bool part_captured = false;
   std::vector<uint8_t*> part_kept;
+  // A server's thread runs this call: it calls the allocator for a request that
+  // is larger than a full batch at most, not for the workspace above.
+  bool served = false;
   // host-side upper bounds (exact after any synchronizing call)
   int64_t live_ub = 0;
   int64_t used_ub = 0;

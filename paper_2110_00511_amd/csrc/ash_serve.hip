@@ -320,7 +320,9 @@ void worker_loop(ash_server* s) {
     const int kind = run[0]->r.kind;
     int64_t total = 0;
     for (Req* q : run) total += q->r.n;
+    m->served = true;
     ash_status_t rc = run.size() == 1 ? run_one(s, run[0]) : run_fused(s, run, s->stages[stage]);
+    m->served = false;
     // counters after the batch (a find changes neither t nor the occupied slots)
     const bool snap = kind != ASH_REQ_FIND;
     if (hipEventRecord(ev, s->stream) != hipSuccess && rc == ASH_OK) rc = ASH_E_DEVICE;

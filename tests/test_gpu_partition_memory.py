@@ -126,3 +126,26 @@ def test_short_of_memory_beside_the_workspace(ash, call):
     finally:
         L.check(L.load().ash_destroy(h), "ash_destroy")
     assert not budget.blocks
+
+
+def test_a_server_allocates_nothing_for_a_batch(ash):
+    """A served insert that would go by bins, on an empty map and no larger than
+    a full batch: the server's thread does not call the allocator."""
+    n = INSERT_MIN + 5
+    keys = np.random.default_rng(3).integers(0, 110, size=(n, 3), dtype=np.int32)
+    m = ash.HashSet(n // 2, 3)
+    srv = ash.Server(m)
+    held = set(m._alloc.blocks)
+    k = torch.from_numpy(keys).cuda()
+    idx = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    mask = torch.full((n,), 7, dtype=torch.uint8, device="cuda")
+    r, keep = srv.request(srv.INSERT, k, out_idx=idx, out_mask=mask)
+    _, status, _ = srv.replay([r], [0.0])
+    assert status[0] == 0
+    assert set(m._alloc.blocks) == held
+    srv.close()
+    orc = OracleMap(n // 2, 3)
+    _, oi, om = orc.activate(keys)
+    assert np.array_equal(idx.cpu().numpy(), oi) and np.array_equal(mask.cpu().numpy(), om)
+    m.clear()
+    assert torch.equal(m.activate(k)[0], idx)  # (no longer served: by bins)
