@@ -1136,13 +1136,29 @@ __global__ __launch_bounds__(kBlock) void k_place_spilled(PartPlan pl, PartRanks
 
 inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 
-constexpr uint32_t kScatterLds = 160 * 1024 - 256;
+constexpr uint32_t kMostLds = 160 * 1024 - 256;  // (the kernels' static LDS is under 256 bytes)
+
+// Lets a kernel be launched with up to kMostLds of dynamic LDS.  The limit
+// belongs to the kernel and not to a launch, and several host threads may be
+// launching it on batches of different sizes, so it is always set to the same
+// value; and before a call's first kernel, so that a failure changes nothing.
+template <typename K>
+hipError_t allow_lds(K* kernel) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)kMostLds);
+}
+
+template <int KD, typename Src, bool kVoxel>
+hipError_t allow_scatter_lds() {
+  if (KD <= 3) {
+    const hipError_t e = allow_lds(k_part_scatter<KD, Src, kVoxel, KD <= 3 ? 8 : 4>);
+    if (e != hipSuccess) return e;
+  }
+  return allow_lds(k_part_scatter<KD, Src, kVoxel, 4>);
+}
 
 template <int KD, typename Src, bool kVoxel, uint32_t kItems>
 hipError_t scatter(const Src& src, const PartPlan& pl, const uint32_t* link, uint32_t lds, hipStream_t st) {
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_part_scatter<KD, Src, kVoxel, kItems>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_part_scatter<KD, Src, kVoxel, kItems>), dim3(pl.nrange), dim3(kCountThreads), lds, st, src, pl,
                      link);
   return hipGetLastError();
@@ -1160,7 +1176,7 @@ hipError_t partition(const Src& src, const PartPlan& pl, uint32_t* link, uint32_
   // tiles of 8 positions per thread where they fit the LDS beside the bins' counters, else of 4
   const uint32_t bins = (2 * pl.nbins + 1) * 4;
   const uint32_t each = ((KD + 1) * 4 + 2) * kCountThreads;
-  if (KD <= 3 && 8 * each + bins <= kScatterLds)
+  if (KD <= 3 && 8 * each + bins <= kMostLds)
     return scatter<KD, Src, kVoxel, KD <= 3 ? 8 : 4>(src, pl, link, 8 * each + bins, st);
   return scatter<KD, Src, kVoxel, 4>(src, pl, link, 4 * each + bins, st);
 }
@@ -1175,7 +1191,10 @@ static_assert(kInsertTable % (kGroup * kDedupThreads) == 0, "whole groups of tab
 template <int KD>
 hipError_t insert_settle(const PartPlan& pl, const PartRanks& pr, const TableRef& tb, const int32_t* keys, Meta* meta,
                          hipStream_t st) {
-  hipError_t e = partition<KD, BatchKeys<KD>, false>(BatchKeys<KD>{keys}, pl, nullptr, nullptr, 0, meta, st);
+  hipError_t e = allow_scatter_lds<KD, BatchKeys<KD>, false>();
+  if (e == hipSuccess) e = allow_lds(k_place<KD>);
+  if (e != hipSuccess) return e;
+  e = partition<KD, BatchKeys<KD>, false>(BatchKeys<KD>{keys}, pl, nullptr, nullptr, 0, meta, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_insert_bins<KD>, dim3(pl.nbins), dim3(kDedupThreads), kInsertTable * 4, st, pl, tb,
                      kInsertTable, meta);
@@ -1199,11 +1218,8 @@ hipError_t insert_store(const PartPlan& pl, const PartRanks& pr, const TableRef&
   // the stage: what a bin is unlikely to exceed, as far as the LDS goes
   const uint32_t mean = cdiv((uint64_t)pl.n << pl.shift, pl.nbuckets);
   const uint32_t slot = SlotWords<KD>::value * 4;
-  const uint32_t stage = std::min((kScatterLds - words * 4) / slot, mean + mean / 8 + 64) & ~3u;
+  const uint32_t stage = std::min((kMostLds - words * 4) / slot, mean + mean / 8 + 64) & ~3u;
   const uint32_t lds = stage * slot + words * 4;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_place<KD>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_place<KD>, dim3(pl.nbins), dim3(kDedupThreads), lds, st, pl, pr, tb, heap, cap, spill,
                      stage);
   hipLaunchKernelGGL(k_place_spilled<KD>, dim3(256), dim3(kBlock), 0, st, pl, pr, tb, heap, spill, meta);
@@ -1267,15 +1283,15 @@ hipError_t launch_voxel_partitioned(const PartPlan& pl, const float* pts, float 
                                     uint64_t* status, hipStream_t st) {
   const uint32_t tiles = cdiv(pl.n, kScanTile), number = cdiv(pl.n, kNumberTile);
   const VoxelKeys src{pts, voxel};
-  hipError_t e = partition<3, VoxelKeys, true>(src, pl, link, reinterpret_cast<uint32_t*>(status), number * 2,
+  hipError_t e = allow_scatter_lds<3, VoxelKeys, true>();
+  if (e == hipSuccess) e = allow_lds(k_voxel_bins);
+  if (e != hipSuccess) return e;
+  e = partition<3, VoxelKeys, true>(src, pl, link, reinterpret_cast<uint32_t*>(status), number * 2,
                                                meta, st);
   if (e != hipSuccess) return e;
   constexpr uint32_t table = 8192;  // about half full of a mean bin's voxels at most
   const uint32_t places = table / 4 * 3;
   const uint32_t lds = table * 8 + places * 2;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_voxel_bins), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_voxel_bins, dim3(pl.nbins), dim3(kDedupThreads), lds, st, pl, table, places, link);
   hipLaunchKernelGGL(k_voxel_number, dim3(number), dim3(kNumberThreads), 0, st, src, pl.n, link, voxel_keys, counts,
                      point_voxel, meta, status);
