@@ -54,6 +54,7 @@ ash_status_t read_meta(ash_map* m, Meta* out, hipStream_t st) {
   ASH_HIP(hipStreamSynchronize(st));
   m->live_ub = out->t;
   m->used_ub = out->used;
+  m->mirror_h->used = out->used;  // nothing is in flight that would write it
   return ASH_OK;
 }
 
@@ -143,6 +144,7 @@ ash_status_t rebuild_table(ash_map* m, int64_t live, hipStream_t st, int64_t roo
   ASH_HIP(hipMemcpyAsync(m->meta, &h, sizeof(Meta), hipMemcpyHostToDevice, st));
   ASH_HIP(hipStreamSynchronize(st));
   m->used_ub = live;
+  m->mirror_h->used = (uint32_t)live;
   m->tombs_possible = false;
   return h.result ? ASH_E_CAPACITY : ASH_OK;  // this rebuild found no slot for some key
 }
@@ -334,6 +336,44 @@ bool part_plan(ash_map* m, int64_t n, ash::PartPlan* pl, ash::PartRanks* pr, hip
   return true;
 }
 
+// Whether an insert or erase of n positions runs as one block (ash_small.hip).
+// That is one launch in place of two, but one lane follows each key's probe
+// sequence, on one CU, where the general kernels give a key G lanes (or a lane
+// a bucket of W slots) and spread the batch; so it is for batches that are
+// small for how full the table is. Whole calls, one block against general,
+// us: an erase of n absent keys / an insert and erase of n new ones, on
+// 333,333 slots that are
+//             a quarter in use           a half                     0.7
+//   W 2 g 1   1000  8, 9 / 20, 25        1000 12, 10 /  30,  37     1000 24, 20 /  51, 69
+//             2048 12, 9 / 31, 28        1500 14, 11 /  32,  38     2048 36, 22 /  80, 71
+//   W 4 g 1   1500  9, 9 / 23, 24         500  8,  9 /  19,  25      500 21, 16 /  45, 51
+//   W 8 g 1   1000  9, 9 / 22, 25         500  8,  9 /  21,  26      200 13, 11 /  32, 36
+//   W 4 g 4   1000  8, 9 / 21, 22         500  8,  9 /  19,  22      500 21, 12 /  45, 38
+//   W16 g16   1000 10, 9 / 26, 21         500  9,  9 /  22,  21      200 16,  9 /  37, 22
+//   W64 g64    500 10, 9 / 22, 21        1000 24,  9 /  54,  22      200 12,  9 /  27, 21
+// In a small table a batch of many new keys makes long chains of CAS on
+// neighboring slots, which one block settles in LDS (8,889 slots, W 4 g 4,
+// 1000 keys: 57 against 75 us from a half in use, 118 against 157 from 0.7).
+// How full the table is comes from bounds (the host's, and the counters of the
+// last insert or erase that ran); results do not depend on the choice.
+// Captured calls are always one block: a replay meets another table.
+bool one_block(const ash_map* m, int64_t n, hipStream_t st) {
+  if (n > (int64_t)ash::kSmallBatch) return false;
+  // most positions with up to 1/4, 1/2, 5/8, 3/4 and more of the slots in use
+  static constexpr int64_t kMost[5][5] = {{1536, 1536, 1536, 1024, 512},  // one lane per key, W = 2
+                                          {1536, 768, 768, 512, 256},     // W = 4
+                                          {1024, 384, 384, 256, 128},     // W = 8
+                                          {1024, 512, 256, 0, 0},         // several lanes per key
+                                          {512, 256, 128, 0, 0}};         // on buckets of 32 slots and more
+  const volatile Meta* mr = m->mirror_h;
+  const int64_t used = 8 * std::min<int64_t>(m->used_ub, mr->used), slots = m->nslots;
+  const int row = m->G > 1 ? (m->W < 32 ? 3 : 4) : (m->W <= 2 ? 0 : (m->W <= 4 ? 1 : 2));
+  const int col = used <= 2 * slots ? 0 : (used <= 4 * slots ? 1 : (used <= 5 * slots ? 2 : (used <= 6 * slots ? 3 : 4)));
+  int64_t most = kMost[row][col];
+  if (16 * n >= slots) most = m->G <= 4 ? std::max<int64_t>(2 * most, 1024) : 2 * most;
+  return n <= most || capturing(st);
+}
+
 ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void* const* values, int32_t* out_idx,
                          uint8_t* out_mask, hipStream_t st, const RequestSource* rs) {
   if (rs) {
@@ -448,7 +488,7 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
   }
   ash::PartPlan pl;
   ash::PartRanks pr;
-  if (!rs && n <= (int64_t)ash::kSmallBatch) {
+  if (!rs && one_block(m, n, st)) {
     uint32_t row_total = 0;
     for (int j = 0; j < vs.n; ++j) row_total += vs.row_bytes[j];
     uint32_t* wlist = row_total >= kSplitRowBytes ? reinterpret_cast<uint32_t*>(m->aux) : nullptr;
@@ -506,7 +546,7 @@ ash_status_t erase_impl(ash_map* m, const int32_t* keys, int64_t n, uint8_t* out
   if (n == 0) return ASH_OK;
   ASH_TRY(ensure_scratch(m, n, st));
   const uint32_t un = (uint32_t)n;
-  if (!rs && n <= (int64_t)ash::kSmallBatch) {
+  if (!rs && one_block(m, n, st)) {
     m->tombs_possible = true;
     ASH_HIP(timed(m, "erase_small", st, [&] {
       return ash::launch_erase_small(m->key_dim, m->ref(), keys, un, m->heap, out_mask, m->meta, st);

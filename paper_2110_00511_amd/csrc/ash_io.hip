@@ -232,6 +232,7 @@ ash_status_t ash_load(const char* path, const ash_allocator_t* allocator, const 
   }
   m->live_ub = t;
   m->used_ub = t;
+  m->mirror_h->used = (uint32_t)t;
   *out = m;
   return ASH_OK;
 }

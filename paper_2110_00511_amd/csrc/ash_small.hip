@@ -6,11 +6,8 @@
 // dropped there, the new keys (or the erased ones) are ranked with block
 // barriers instead of a look-back, and nothing goes through scratch memory.
 // One launch per call, and the table is written only once it is known that the
-// batch fits.  Insert (kernel time, int32x3 keys with 4-byte rows, over
-// tombstones and not) and erase, two launches against one, W = 4, four lanes
-// per key: 300 keys 29 -> 10 and 15 -> 7 us, 1000 keys 30 -> 14 and 16 -> 8 us,
-// 2000 keys 33 -> 20 and 18 -> 11 us.  At 4000 keys one CU takes as long as
-// the spread kernels (33 / 32 us; key width 4 longer), so they go there.
+// batch fits.  Which batches come here, with both sides' times: one_block in
+// ash_api.hip.
 #include "ash_device.hpp"
 #include "ash_launch.hpp"
 
