@@ -245,31 +245,52 @@ ValueSet make_values(const ash_map* m, const void* const* src, void* const* dst,
 }
 
 // An insert into an empty map goes by hash bins (ash_partition.hip) from this
-// many positions on, where the table is at most kPartTableRatio times as large
-// (its parts are written whole) and enough of the positions bring new keys:
-// that path does the same for a new key as for a repeat, while the general path
-// spends a CAS and a random store on each new key and little on a repeat.
+// many positions on, where the table is not too large for the batch (its parts
+// are written whole) and enough of the positions bring new keys: that path does
+// the same for a new key as for a repeat, while the general path spends a CAS
+// and a random store on each new key and little on a repeat.
 // Clear + insert, general path against bins, int32x3 keys, W = 2, one lane per key:
 //   1M positions, half new 97 / 91 us, 2M 149 / 143, 4M 302 / 235, 10M 712 / 543;
 //   10M, 10% new 396 / 468, 20% 495 / 504, 30% 587 / 505, 99% 984 / 569;
 //   2.1M, 20% new 125 / 137, 40% 151 / 145, 99% 212 / 159.
-// Key width 4 moves entries of 32 bytes: 4M, 45% new 332 / 344, 99% 487 / 371.
+// (So batches of 1M to 2.6M of mostly new keys would gain as well; the line
+// lies where those with few do not lose.)  Inserts alone, general / bins, by
+// slots per position and share of new keys, the general path knowing the share
+// from an insert before:
+//                       2%         10%        30%        50%        99%
+//   2.7M, 2 slots     81 / 131  105 / 138  134 / 150  168 / 152  194 / 156   W = 2, g = 1
+//         4           84 / 152  109 / 159  150 / 169  186 / 172  245 / 178
+//         8           89 / 192  125 / 198  185 / 213  213 / 215  253 / 216
+//   6M,   2          185 / 258  243 / 278  365 / 300  418 / 302  537 / 321   W = 4, g = 4
+//         4          182 / 297  250 / 314  369 / 339  431 / 343  502 / 353
+//         8          184 / 373  254 / 386  367 / 408  433 / 410  554 / 416
+// and not knowing it (a map's first insert, whose claim cannot keep its pending
+// keys), 2.7M at W = 4, g = 4:
+//         0.35       107 / 118  142 / 127
+//         2          107 / 131  139 / 136  164 / 147  173 / 146  203 / 158
+//         4          107 / 148  137 / 158  169 / 169  196 / 170  256 / 178
+//         8          114 / 191  147 / 201  191 / 216  222 / 214  249 / 217
+// Key width 4 moves entries and slots of 32 bytes (W = 4, g = 4):
+//   2.7M, 2          147 / 218 (10%)      212 / 234  266 / 233 (80%)  299 / 226
+//         4          155 / 259            244 / 263  289 / 266        285 / 275
+//         8          158 / 314            250 / 339  275 / 362        259 / 377
 // Into a table that holds keys, every key has to be looked up in it too: a
 // second insert of 2.7M takes 242 / 275 us, of 10M 957 / 835 with W = 2 and
 // 896 / 921 with W = 4, four lanes per key, all new, and 849 / 857 and
 // 827 / 964 half new; so only the empty table's goes by bins.  An erase by bins
 // (lookups, no new keys' stores) took 438 against 379 us for 5M.
-// The last finalized insert's fraction decides; where there was none, widths
-// 1 to 3 go by bins (a first insert cannot keep its pending keys either: 10M
-// with 10% new take about 530 us on the general path then).
+// The last finalized insert's fraction decides, if it was an insert of some
+// size against this one; up to four slots per position widths 1 to 3 go by bins
+// without one, since few new keys in a map with room for many times as many
+// lose less than many new keys gain.
 constexpr int64_t kInsertPartMin = 5 << 19;
-constexpr int64_t kPartTableRatio = 8;
 
 bool insert_by_bins(const ash_map* m, int64_t n, uint64_t last_n, uint64_t last_new) {
-  if (m->used_ub > 0) return false;
-  if (n < kInsertPartMin || (int64_t)m->nslots > kPartTableRatio * n) return false;
-  if (m->key_dim == 4) return last_n > 0 && last_new * 10 >= last_n * 8;
-  return last_n == 0 || last_new * 100 > last_n * 35;
+  if (m->used_ub > 0 || n < kInsertPartMin) return false;
+  const int64_t slots = m->nslots;
+  if (m->key_dim == 4) return slots <= 4 * n && last_n > 0 && last_new * 10 >= last_n * 8;
+  if (last_n * 16 < (uint64_t)n) return slots <= 4 * n;
+  return (slots <= 4 * n && last_new * 100 > last_n * 35) || (slots <= 8 * n && last_new * 2 >= last_n);
 }
 
 // Whether work on st is being captured.  (Asked of the null stream while
