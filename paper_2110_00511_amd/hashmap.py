@@ -380,10 +380,13 @@ def autotune(capacity, n_insert, distinct_ratio, key_dim=3, value_specs=(), devi
 
 def batched(ops, fused=True):
     """Inserts then finds on many maps at once (one persistent launch when
-    fused).  ops: list of dicts with keys map, insert_keys, insert_values,
+    fused).  ops: sequence of dicts with keys map, insert_keys, insert_values,
     find_keys, gather (bool).  Returns a list of dicts with insert_idx,
-    insert_mask, find_idx, find_mask and find_values."""
+    insert_mask, find_idx, find_mask and find_values.  The maps' index tensors
+    are parts of one tensor, and so are their masks: clone() one to keep or
+    save it without the others' memory."""
     lib = L.load()
+    ops = list(ops)
     arr = (L.AshBatchOp * max(len(ops), 1))()
     keep = []
     calls = []
@@ -396,7 +399,8 @@ def batched(ops, fused=True):
         if len(vals) != len(m.value_specs):
             raise ValueError("one value tensor per value buffer is required")
         calls.append((m, ik, ni, vals, fk, fk.shape[0]))
-    # the maps' results are parts of one tensor of each kind
+    # the maps' results are parts of one tensor of each kind: 256 tensors of their
+    # own take the host 430 us for 64 maps, whose whole call takes 3150, these 120
     device = calls[0][0].device if calls else None
     if all(c[0].device == device for c in calls):
         sizes = [c[2] for c in calls] + [c[5] for c in calls]
