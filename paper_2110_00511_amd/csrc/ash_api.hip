@@ -531,7 +531,7 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
     uint32_t* wlist = row_total >= kSplitRowBytes ? reinterpret_cast<uint32_t*>(m->aux) : nullptr;
     ASH_HIP(timed(m, "commit", st, [&] {
       return ash::launch_insert_store(m->key_dim, pl, pr, m->ref(), keys, m->kB, m->heap, (uint32_t)m->c, vs, out_idx,
-                                      out_mask, m->meta, wlist, m->slot_of, 0, st);
+                                      out_mask, m->meta, wlist, m->slot_of, st);
     }));
     if (wlist)
       ASH_HIP(timed(m, "values", st, [&] {
@@ -1087,7 +1087,7 @@ bool voxel_part_work(int64_t n, VoxelPartWork* w) {
   pl.nbuckets = pl.nbins;
   pl.shift = 0;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  w->tiles = (n + ash::kScanTile - 1) / ash::kScanTile;
+  w->tiles = (n + ash::kNumberTile - 1) / ash::kNumberTile;
   size_t o = 0;
   w->hist = o;
   o += up((size_t)pl.nrange * pl.nbins * 4);

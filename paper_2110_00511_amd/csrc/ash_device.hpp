@@ -508,6 +508,7 @@ constexpr uint32_t kPartTile = 1u << kPartTileLog2;  // positions whose copies a
 constexpr uint32_t kPartRanges = 256;    // most ranges
 constexpr uint32_t kPartBins = 4096;     // most bins
 constexpr uint32_t kVoxelBinMean = 3840; // most points per bin of a voxelization, on average
+constexpr uint32_t kNumberTile = 4096;   // points that are numbered together
 // A point's link while a partitioned voxelization runs (positions < 2^30).
 constexpr uint32_t kVoxelWinner = 0x80000000u;  // + the voxel's count: the first point of its voxel
 constexpr uint32_t kVoxelLocal = 0x40000000u;   // + the position of the range's point it repeats

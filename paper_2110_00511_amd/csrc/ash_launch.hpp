@@ -133,10 +133,10 @@ hipError_t launch_insert_settle(int kd, const PartPlan& pl, const PartRanks& pr,
 hipError_t launch_insert_store(int kd, const PartPlan& pl, const PartRanks& pr, const TableRef& tb,
                                const int32_t* keys, int32_t* kB, const int32_t* heap, uint32_t cap, const ValueSet& vs,
                                int32_t* out_idx, uint8_t* out_mask, Meta* meta, uint32_t* wlist, uint32_t* spill,
-                               int silent, hipStream_t st);
+                               hipStream_t st);
 // A whole voxelization by hash bins: the plan's n / nbins must be at most
-// 2 * kVoxelBinMean; link is n words, status a word pair per 1024 points (both
-// need no initial state).  Writes what launch_voxel_commit and
+// 2 * kVoxelBinMean; link is n words, status a word pair per kNumberTile points
+// (both need no initial state).  Writes what launch_voxel_commit and
 // launch_voxel_resolve write; meta->claims is the number of voxels.
 hipError_t launch_voxel_partitioned(const PartPlan& pl, const float* pts, float voxel, uint32_t* link,
                                     int32_t* voxel_keys, int32_t* counts, int32_t* point_voxel, Meta* meta,

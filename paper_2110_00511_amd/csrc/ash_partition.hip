@@ -570,8 +570,7 @@ __global__ __launch_bounds__(kDedupThreads, 8) void k_voxel_bins(PartPlan pl, ui
 // 4096 points are a quarter as many steps as tiles of 1024 (5M points at 5 mm
 // 59 -> 51 us, at 5 cm 41 -> 43; whole calls on 0.7M points and more 0 to 4%
 // faster, smaller ones the same).
-constexpr uint32_t kNumberThreads = 1024;
-constexpr uint32_t kNumberTile = kNumberThreads * kScanItems;
+constexpr uint32_t kNumberThreads = kNumberTile / kScanItems;
 
 __global__ __launch_bounds__(kNumberThreads) void k_voxel_number(VoxelKeys src, uint32_t n, const uint32_t* __restrict__ link,
                                                          int32_t* __restrict__ voxel_keys,
@@ -914,7 +913,7 @@ __global__ __launch_bounds__(kBlock) void k_part_commit(PartPlan pl, PartRanks p
                                                         const int32_t* __restrict__ keys, int32_t* __restrict__ kB,
                                                         const int32_t* __restrict__ heap, uint32_t cap, ValueSet vs,
                                                         int32_t* __restrict__ out_idx, uint8_t* __restrict__ out_mask,
-                                                        Meta* meta, uint32_t* __restrict__ wlist, int silent) {
+                                                        Meta* meta, uint32_t* __restrict__ wlist) {
   __shared__ uint2 s_pairs[kInline ? kScanTile : 1];
   __shared__ uint32_t s_two[2 * (kBlock / 64)];
   const uint32_t base = blockIdx.x * kScanTile;
@@ -936,7 +935,7 @@ __global__ __launch_bounds__(kBlock) void k_part_commit(PartPlan pl, PartRanks p
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (overflow) {
       meta->result = 0;
-      if (!silent) __hip_atomic_fetch_or(&meta->status, kStatusCapacity, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_or(&meta->status, kStatusCapacity, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       meta->t = t0 + total;
       meta->used += total;  // a bound: tombstones may be taken
@@ -1205,14 +1204,14 @@ hipError_t insert_settle(const PartPlan& pl, const PartRanks& pr, const TableRef
 template <int KD>
 hipError_t insert_store(const PartPlan& pl, const PartRanks& pr, const TableRef& tb, const int32_t* keys, int32_t* kB,
                         const int32_t* heap, uint32_t cap, const ValueSet& vs, int32_t* out_idx, uint8_t* out_mask,
-                        Meta* meta, uint32_t* wlist, uint32_t* spill, int silent, hipStream_t st) {
+                        Meta* meta, uint32_t* wlist, uint32_t* spill, hipStream_t st) {
   const dim3 tiles(cdiv(pl.n, kScanTile));
   if (wlist)
     hipLaunchKernelGGL((k_part_commit<KD, false>), tiles, dim3(kBlock), 0, st, pl, pr, tb, keys, kB, heap, cap, vs,
-                       out_idx, out_mask, meta, wlist, silent);
+                       out_idx, out_mask, meta, wlist);
   else
     hipLaunchKernelGGL((k_part_commit<KD, true>), tiles, dim3(kBlock), 0, st, pl, pr, tb, keys, kB, heap, cap, vs,
-                       out_idx, out_mask, meta, wlist, silent);
+                       out_idx, out_mask, meta, wlist);
   const uint32_t region = tb.bucket_width << pl.shift;
   const uint32_t words = (region + 31u) / 32u + pl.nrange + 1 + (region + 1u) / 2u;
   // the stage: what a bin is unlikely to exceed, as far as the LDS goes
@@ -1242,12 +1241,12 @@ hipError_t launch_insert_settle(int kd, const PartPlan& pl, const PartRanks& pr,
 hipError_t launch_insert_store(int kd, const PartPlan& pl, const PartRanks& pr, const TableRef& tb,
                                const int32_t* keys, int32_t* kB, const int32_t* heap, uint32_t cap, const ValueSet& vs,
                                int32_t* out_idx, uint8_t* out_mask, Meta* meta, uint32_t* wlist, uint32_t* spill,
-                               int silent, hipStream_t st) {
+                               hipStream_t st) {
   switch (kd) {
-    case 1: return insert_store<1>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, silent, st);
-    case 2: return insert_store<2>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, silent, st);
-    case 3: return insert_store<3>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, silent, st);
-    case 4: return insert_store<4>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, silent, st);
+    case 1: return insert_store<1>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, st);
+    case 2: return insert_store<2>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, st);
+    case 3: return insert_store<3>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, st);
+    case 4: return insert_store<4>(pl, pr, tb, keys, kB, heap, cap, vs, out_idx, out_mask, meta, wlist, spill, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1256,14 +1255,14 @@ bool part_buckets(PartPlan* pl, uint32_t nbuckets, uint32_t bucket_width) {
   pl->nbuckets = nbuckets;
   pl->shift = 0;
   const auto bins = [&] { return (uint32_t)(((uint64_t)nbuckets + (1ull << pl->shift) - 1) >> pl->shift); };
-  // the largest bins that keep every CU busy, of at most kInsertBinMean positions on average
-  const uint64_t mean = std::min<uint64_t>(kInsertBinMean, std::max<uint64_t>(pl->n / 256, 1024));
-  while (pl->shift < 31 && (uint64_t)pl->n << (pl->shift + 1) <= mean * nbuckets) ++pl->shift;
+  // the largest bins of at most kInsertBinMean positions on average (more than one per CU from 2.6M on)
+  const uint64_t most = (uint64_t)kInsertBinMean * nbuckets;
+  while (pl->shift < 31 && (uint64_t)pl->n << (pl->shift + 1) <= most) ++pl->shift;
   pl->nbins = bins();
   // a table of few buckets (of a few thousand slots, against at least 2.6M
   // positions) has no bins that small: entries beyond a bin's LDS table are
   // settled by a scan of the bin, quadratic in what does not fit it
-  if ((uint64_t)pl->n << pl->shift > (uint64_t)kInsertBinMean * nbuckets) return false;
+  if ((uint64_t)pl->n << pl->shift > most) return false;
   // a bin's part of the table has a bit per slot in LDS
   return pl->nbins <= kPartBins && ((uint64_t)bucket_width << pl->shift) <= kPartMostRegion;
 }
