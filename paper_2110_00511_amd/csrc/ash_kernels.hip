@@ -2005,7 +2005,17 @@ hipError_t launch_sum_partials(const uint32_t* partial, uint32_t count, Meta* me
 // full tile of 256 positions keeps each group busy for G positions in turn: G
 // chains of dependent loads one after another.  That is right for large
 // batches (one block per 256 positions) and only latency for small ones, so a
-// batch of few tiles is spread until there are about 1024 blocks.
+// batch of few tiles is spread until there are about 1024 blocks.  Kernel time,
+// full tiles against spread, us, 200,000 keys in a map for 400,000 with a value
+// of 4 bytes:
+//                     find                        insert / erase
+//            3000 keys   50,000    150,000    3000          50,000
+//   g = 1    8.4 / 7.9   12 / 12   34 / 34    47 / 45       87 / 85
+//   g = 4    8.5 / 6.1   10 / 6.3  15 / 11    47 / 33       58 / 46
+//   g = 16    17 / 6.2   20 / 8.6  27 / 19    72 / 32       85 / 53
+//   g = 64    49 / 6.1   57 / 20   72 / 48    182 / 34      205 / 83
+// Neighbor searches of 300 and 3000 queries for 27 cells: g = 4 9.8 / 6.2 and 11
+// / 7.4, g = 64 42 / 6.2 and 63 / 29; a rebuild takes the same time either way.
 constexpr uint32_t kSpreadBlocks = 1024;
 
 static inline uint32_t rounds_of(uint32_t g, uint32_t n) {

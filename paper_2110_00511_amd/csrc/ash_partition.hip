@@ -80,9 +80,12 @@ __device__ __forceinline__ uint32_t copies_per_entry(const PartPlan& pl) { retur
 // for the positions that go to a bin.  Voxel batches also get each position's link:
 // kVoxelWinner + number of copies for a position that goes to a bin, else
 // kVoxelLocal + the position it repeats, or kNoSlot for a rejected point.
-// Bound by arithmetic (the hash, three divisions for a point) and LDS latency:
-// 35 us at 5M points (50 at 10M keys), whose streams alone take 16.  One block of 16 waves per
-// CU; the next tile's keys are loaded while the current one is worked on.
+// 33 to 35 us at 5M points (55 at 10M keys), whose streams alone take 16.  By
+// counters no unit is full: VALU 52% busy (35% for keys: the hash, and three
+// divisions for a point), LDS 16% (half of it bank conflicts), memory at 2.2
+// TB/s, and waves wait 55 to 62% of their time, for LDS and at the barriers
+// between a tile's steps.  One block of 16 waves per CU (the LDS holds no
+// more); the next tile's keys are loaded while the current one is worked on.
 template <int KD, typename Src, bool kVoxel>
 __global__ __launch_bounds__(kCountThreads) void k_part_count(Src src, PartPlan pl, uint32_t* __restrict__ link,
                                                               uint32_t* __restrict__ zero, uint32_t n_zero,
@@ -259,7 +262,10 @@ __device__ __forceinline__ void block_scan_into(const uint32_t* __restrict__ v, 
 // in its range's run.  A tile's entries are first put in bin order in LDS, so
 // that a run's entries of one tile (about 6 with 1400 bins) leave together:
 // written one by one they reach memory as 16-byte stores (88 G/s; 149 us at
-// 10M keys).  kItems positions per thread and tile: as many as the LDS holds.
+// 10M keys, against 111).  kItems positions per thread and tile: as many as the
+// LDS holds.  Bound by latency like the count, with one block per CU: memory
+// moves at 2.8 TB/s, VALU is 17% busy (36% for points), LDS 18%, and waves wait
+// two thirds of their time.
 template <int KD, typename Src, bool kVoxel, uint32_t kItems>
 __global__ __launch_bounds__(kCountThreads) void k_part_scatter(Src src, PartPlan pl,
                                                                 const uint32_t* __restrict__ link) {
@@ -468,12 +474,14 @@ __device__ __forceinline__ void bin_place(const BinTable& t, const uint32_t* ent
 // point's count (where copies came in from other tiles), and every other
 // point's first point.  The table has room for twice the mean bin; an entry
 // that finds it full (a bin of many times the mean's distinct voxels) is
-// settled by a scan over the bin.  Bound by LDS and L2 latency: a wave waits
-// for its longest probe sequence, so the table hashes twice (linear probing:
-// 324 against 130 us at 5M points), and two blocks of 16 waves share a CU (76
-// KB each; one block with twice the bin: 130 against 66 us; bins of 2560 and
-// 1900 points gain here what the scatter's shorter runs lose).  A thread works
-// on two entries at once: four need 73 registers, or spill at 64 (144 us).
+// settled by a scan over the bin.  Bound by arithmetic and LDS latency (VALU 45%
+// busy, LDS 18%, waves wait 55% of their time, memory 2.1 TB/s; at 5 cm links
+// written to random places make it 3.8): a wave waits for its longest
+// probe sequence, so the table hashes twice (linear probing: 324 against 130 us
+// at 5M points), and two blocks of 16 waves share a CU (76 KB each; one block
+// with twice the bin: 130 against 66 us; bins of 2560 and 1900 points gain here
+// what the scatter's shorter runs lose).  A thread works on two entries at once:
+// four need 73 registers, or spill at 64 (144 us).
 __global__ __launch_bounds__(kDedupThreads, 8) void k_voxel_bins(PartPlan pl, uint32_t table, uint32_t places,
                                                               uint32_t* __restrict__ link) {
   constexpr int KD = 3;
@@ -566,7 +574,8 @@ __global__ __launch_bounds__(kDedupThreads, 8) void k_voxel_bins(PartPlan pl, ui
 
 // First points are ranked in batch order (the voxel ids) and write their
 // voxel's key and count, their own id, and -1 for rejected points.  Bound by
-// the look-back between tiles, whose words travel through memory: tiles of
+// the look-back between tiles, whose words travel through memory (waves wait 76%
+// of their time, memory moves at 3.6 TB/s at 5 mm and 1.0 at 5 cm): tiles of
 // 4096 points are a quarter as many steps as tiles of 1024 (5M points at 5 mm
 // 59 -> 51 us, at 5 cm 41 -> 43; whole calls on 0.7M points and more 0 to 4%
 // faster, smaller ones the same).
@@ -695,7 +704,8 @@ __device__ __forceinline__ void table_holds(const TableRef& tb, const int32_t (&
 // One bin's new keys: the lowest position of each key in the bin, where the
 // table does not hold it.  All other entries get kPartLost.  An entry that
 // finds the LDS table full is settled by a scan over the bin.  Bound like
-// k_voxel_bins by LDS and L2 latency and by the hash.  A table that holds keys
+// k_voxel_bins by arithmetic (the hash; VALU 50% busy) and LDS latency: 97 us at
+// 10M keys, 1.7 TB/s.  A table that holds keys
 // costs a lookup per key on top, which makes the general path the faster one;
 // a captured insert may be replayed on one all the same.
 template <int KD>
@@ -777,8 +787,8 @@ __global__ __launch_bounds__(kDedupThreads, 8) void k_insert_bins(PartPlan pl, T
 // Every entry's rank (with its range above it; kNoSlot for one that is no new
 // key) goes to entry_rank, beside the entries, for the kernel that stores the
 // bins: there a lookup of the bits by position missed the L2 for most keys.
-// Also keeps the counters that the commit changes.  Bound by reading the
-// entries once more, in coalesced runs.
+// Also keeps the counters that the commit changes.  Bound by memory: 53 us at
+// 10M keys, 4.4 TB/s (the entries' lines once more, for their last words).
 template <int KD>
 __global__ __launch_bounds__(1024) void k_part_collect(PartPlan pl, PartRanks pr, const Meta* meta) {
   constexpr int S = kEntryWords<KD>;
@@ -908,6 +918,7 @@ __device__ __forceinline__ uint32_t rank_in(const uint4& rec, uint32_t p) {
 // k^B[i] and their rows, every position its index and mask.  Each tile knows
 // its ranks from the range's totals, so tiles do not wait for each other.
 // The first tile moves t; later kernels read the counters kept by collect.
+// Bound by memory: 81 us at 10M new keys with 4-byte rows, 5.1 TB/s.
 template <int KD, bool kInline>
 __global__ __launch_bounds__(kBlock) void k_part_commit(PartPlan pl, PartRanks pr, TableRef tb,
                                                         const int32_t* __restrict__ keys, int32_t* __restrict__ kB,
@@ -994,7 +1005,8 @@ struct RankIndex {
 // into an empty table the EMPTY ones with them, as whole lines: random 16-byte
 // stores took 161 us for 5M keys in 188 MB and 258 us for 10M in 384 MB.  The
 // few keys that reach the end of the part go to the list `spill`, for
-// k_place_spilled.
+// k_place_spilled.  Bound by memory: 114 us for 10M in 384 MB, 5.1 TB/s, the rate
+// of a large copy.
 template <int KD>
 __global__ __launch_bounds__(kDedupThreads) void k_place(PartPlan pl, PartRanks pr, TableRef tb,
                                                          const int32_t* __restrict__ heap, uint32_t cap,
