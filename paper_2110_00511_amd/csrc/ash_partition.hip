@@ -1159,19 +1159,28 @@ hipError_t allow_lds(K* kernel) {
                              (int)kMostLds);
 }
 
+// LDS of a scatter in tiles of `items` positions per thread.
+template <int KD>
+uint32_t scatter_lds(const PartPlan& pl, uint32_t items) {
+  return items * ((KD + 1) * 4 + 2) * kCountThreads + (2 * pl.nbins + 1) * 4;
+}
+
+// Tiles of 8 positions per thread where they fit the LDS beside the bins' counters, else of 4.
+template <int KD>
+bool wide_tiles(const PartPlan& pl) {
+  return KD <= 3 && scatter_lds<KD>(pl, 8) <= kMostLds;
+}
+
 template <int KD, typename Src, bool kVoxel>
-hipError_t allow_scatter_lds() {
-  if (KD <= 3) {
-    const hipError_t e = allow_lds(k_part_scatter<KD, Src, kVoxel, KD <= 3 ? 8 : 4>);
-    if (e != hipSuccess) return e;
-  }
-  return allow_lds(k_part_scatter<KD, Src, kVoxel, 4>);
+hipError_t allow_scatter_lds(const PartPlan& pl) {
+  return wide_tiles<KD>(pl) ? allow_lds(k_part_scatter<KD, Src, kVoxel, KD <= 3 ? 8 : 4>)
+                            : allow_lds(k_part_scatter<KD, Src, kVoxel, 4>);
 }
 
 template <int KD, typename Src, bool kVoxel, uint32_t kItems>
-hipError_t scatter(const Src& src, const PartPlan& pl, const uint32_t* link, uint32_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((k_part_scatter<KD, Src, kVoxel, kItems>), dim3(pl.nrange), dim3(kCountThreads), lds, st, src, pl,
-                     link);
+hipError_t scatter(const Src& src, const PartPlan& pl, const uint32_t* link, hipStream_t st) {
+  hipLaunchKernelGGL((k_part_scatter<KD, Src, kVoxel, kItems>), dim3(pl.nrange), dim3(kCountThreads),
+                     scatter_lds<KD>(pl, kItems), st, src, pl, link);
   return hipGetLastError();
 }
 
@@ -1184,12 +1193,8 @@ hipError_t partition(const Src& src, const PartPlan& pl, uint32_t* link, uint32_
   hipLaunchKernelGGL((k_part_count<KD, Src, kVoxel>), dim3(pl.nrange), dim3(kCountThreads), pl.nbins * 4, st, src, pl,
                      link, zero, n_zero, meta);
   hipLaunchKernelGGL(k_part_scan, dim3(cdiv(pl.nbins, 64)), dim3(1024), 0, st, pl);
-  // tiles of 8 positions per thread where they fit the LDS beside the bins' counters, else of 4
-  const uint32_t bins = (2 * pl.nbins + 1) * 4;
-  const uint32_t each = ((KD + 1) * 4 + 2) * kCountThreads;
-  if (KD <= 3 && 8 * each + bins <= kMostLds)
-    return scatter<KD, Src, kVoxel, KD <= 3 ? 8 : 4>(src, pl, link, 8 * each + bins, st);
-  return scatter<KD, Src, kVoxel, 4>(src, pl, link, 4 * each + bins, st);
+  return wide_tiles<KD>(pl) ? scatter<KD, Src, kVoxel, KD <= 3 ? 8 : 4>(src, pl, link, st)
+                            : scatter<KD, Src, kVoxel, 4>(src, pl, link, st);
 }
 
 }  // namespace
@@ -1202,7 +1207,7 @@ static_assert(kInsertTable % (kGroup * kDedupThreads) == 0, "whole groups of tab
 template <int KD>
 hipError_t insert_settle(const PartPlan& pl, const PartRanks& pr, const TableRef& tb, const int32_t* keys, Meta* meta,
                          hipStream_t st) {
-  hipError_t e = allow_scatter_lds<KD, BatchKeys<KD>, false>();
+  hipError_t e = allow_scatter_lds<KD, BatchKeys<KD>, false>(pl);
   if (e == hipSuccess) e = allow_lds(k_place<KD>);
   if (e != hipSuccess) return e;
   e = partition<KD, BatchKeys<KD>, false>(BatchKeys<KD>{keys}, pl, nullptr, nullptr, 0, meta, st);
@@ -1294,7 +1299,7 @@ hipError_t launch_voxel_partitioned(const PartPlan& pl, const float* pts, float 
                                     uint64_t* status, hipStream_t st) {
   const uint32_t tiles = cdiv(pl.n, kScanTile), number = cdiv(pl.n, kNumberTile);
   const VoxelKeys src{pts, voxel};
-  hipError_t e = allow_scatter_lds<3, VoxelKeys, true>();
+  hipError_t e = allow_scatter_lds<3, VoxelKeys, true>(pl);
   if (e == hipSuccess) e = allow_lds(k_voxel_bins);
   if (e != hipSuccess) return e;
   e = partition<3, VoxelKeys, true>(src, pl, link, reinterpret_cast<uint32_t*>(status), number * 2,
