@@ -475,7 +475,10 @@ ash_status_t insert_impl(ash_map* m, const int32_t* keys, int64_t n, const void*
   };
   // The capacity check needs the batch's count of new keys; when the host's
   // bound on t plus n fits in c it cannot fail and the count is skipped.
+  // A captured insert meets another t when it is replayed: one of a size that
+  // may go by bins, which always compare, compares on either path.
   int check = m->live_ub + n > m->c ? 1 : 0;
+  if (n >= kInsertPartMin && !(m->flags & ASH_F_AUTOGROW) && capturing(st)) check = 1;
   if (check && (m->flags & ASH_F_AUTOGROW)) {
     Meta h;
     ASH_TRY(read_meta(m, &h, st));

@@ -70,6 +70,17 @@ def test_a_size_that_has_run_can_be_captured(ash):
             want = in_parts(eager, k)
             assert torch.equal(idx, want[0]) and torch.equal(mask, want[1])
             assert lib.ash_device_status(h, stream()) == 0
+        # replayed on a map that has no room for its keys: refused, the map as it was
+        size = ctypes.c_int64()
+        L.check(lib.ash_clear(h, stream()), "ash_clear")
+        L.check(lib.ash_activate(h, other.data_ptr(), n, None, None, stream()), "ash_activate")
+        L.check(lib.ash_size(h, ctypes.byref(size), stream()), "ash_size")
+        before = size.value
+        graph.replay()
+        assert bool((idx == -1).all()) and not bool(mask.any())
+        assert lib.ash_device_status(h, stream()) == 2
+        L.check(lib.ash_size(h, ctypes.byref(size), stream()), "ash_size")
+        assert size.value == before > n // 2
         del graph
     finally:
         torch.cuda.synchronize()
