@@ -279,17 +279,23 @@ ValueSet make_values(const ash_map* m, const void* const* src, void* const* dst,
 // 896 / 921 with W = 4, four lanes per key, all new, and 849 / 857 and
 // 827 / 964 half new; so only the empty table's goes by bins.  An erase by bins
 // (lookups, no new keys' stores) took 438 against 379 us for 5M.
+// (at 10% and 80% new W = 8, g = 8 takes 201 / 219 and 304 / 225 with 2 slots per
+// position, 213 / 253 and 353 / 265 with 4).
 // The last finalized insert's fraction decides, if it was an insert of some
 // size against this one; up to four slots per position widths 1 to 3 go by bins
 // without one, since few new keys in a map with room for many times as many
-// lose less than many new keys gain.
+// lose less than many new keys gain.  Key width 4 does so only on buckets of 8
+// slots and more, to about 2 slots per position, after a small insert of mostly
+// new keys.
 constexpr int64_t kInsertPartMin = 5 << 19;
 
 bool insert_by_bins(const ash_map* m, int64_t n, uint64_t last_n, uint64_t last_new) {
   if (m->used_ub > 0 || n < kInsertPartMin) return false;
   const int64_t slots = m->nslots;
-  if (m->key_dim == 4) return slots <= 4 * n && last_n > 0 && last_new * 10 >= last_n * 8;
-  if (last_n * 16 < (uint64_t)n) return slots <= 4 * n;
+  const bool word = last_n * 16 >= (uint64_t)n;  // the last insert says something about this one
+  if (m->key_dim == 4)
+    return last_n > 0 && last_new * 10 >= last_n * 8 && (word ? slots <= 4 * n : m->W >= 8 && slots * 4 <= 9 * n);
+  if (!word) return slots <= 4 * n;
   return (slots <= 4 * n && last_new * 100 > last_n * 35) || (slots <= 8 * n && last_new * 2 >= last_n);
 }
 

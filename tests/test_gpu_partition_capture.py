@@ -124,3 +124,52 @@ def test_a_graph_keeps_its_workspace(ash):
         assert m.device_status() == 0
     m.close()
     assert not m._alloc.blocks
+
+
+def test_width_4_replayed(ash):
+    """An insert of key width 4 by bins, captured on an empty map and replayed on
+    an empty one, on one that holds keys, over tombstones and without enough
+    room, gives what the general path gives."""
+    n, key_dim = INSERT_MIN + 5, 4
+    cap = int(1.75 * n)
+    batches = [draw(10, n, key_dim, 0.8 * n), draw(11, n, key_dim, 1.6 * n),
+               draw(12, n, key_dim, 1.2 * n) + (1 << 20), draw(13, n, key_dim, 5 * n) + (1 << 21)]
+    gone = batches[1][:700_001].contiguous()
+    eager = ash.HashSet(cap, key_dim)
+    m = ash.HashSet(cap, key_dim)
+    first = torch.arange(n, dtype=torch.int32, device="cuda")[:, None].repeat(1, key_dim)
+    m.activate(first)  # all new, of the batch's size: the next one goes by bins
+    torch.cuda.synchronize()  # (once the host can read its outcome)
+    m.profile()
+    m.clear()
+    m.activate(first)
+    assert "claim_bins" in m.profile_collect()
+    m.profile(False)
+    m.clear()
+    torch.cuda.synchronize()
+    keys = batches[0].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        idx, mask = m.activate(keys)
+    for _ in range(2):
+        m.clear()
+        eager.clear()
+        for j, k in enumerate(batches):
+            keys.copy_(k)
+            before = eager.size()
+            graph.replay()
+            torch.cuda.synchronize()
+            if j < 3:
+                want = in_parts(eager, k)
+                assert torch.equal(idx, want[0]) and torch.equal(mask, want[1])
+                assert m.device_status() == 0
+            else:
+                assert bool((idx == -1).all()) and not bool(mask.any())
+                assert m.device_status() == 2 and m.size() == before
+            assert m.size() == eager.size()
+            if j == 1:
+                assert torch.equal(m.erase(gone), eager.erase(gone))
+        live = eager.active_indices().long()
+        assert torch.equal(m.active_indices().long(), live)
+        assert torch.equal(m.key_buffer()[live], eager.key_buffer()[live])
+        assert torch.equal(m.heap_buffer(), eager.heap_buffer())

@@ -74,3 +74,21 @@ def test_a_few_keys_say_nothing_of_millions(ash):
             m.activate(many)
             assert ("claim_bins" in m.profile_collect()) == expect, slots
             m.close()
+
+
+@pytest.mark.parametrize("w,g", [(4, 4), (8, 8)])
+def test_width_4_after_a_few_keys(ash, w, g):
+    """Key width 4 takes the word of an insert of 100 new keys on wide buckets only."""
+    n = INSERT_MIN + 9
+    many = spread(n, 0.9)
+    many = torch.cat([many, many[:, :1]], dim=1).contiguous()
+    m = ash.HashSet(n, 4, bucket_width=w, probe_group=g)
+    m.activate(many[:100])
+    m.clear()
+    m.profile()
+    torch.cuda.synchronize()
+    for expect in (w == 8, True):  # then of one of its own size
+        m.clear()
+        m.profile_collect()
+        m.activate(many)
+        assert ("claim_bins" in m.profile_collect()) == expect
