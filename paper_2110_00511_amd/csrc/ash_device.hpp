@@ -149,6 +149,14 @@ struct TableRef {
   Meta* mirror;           // nullable host-mapped copy of the counters, written by every finalize
 };
 
+// Raises the bound on the non-empty slots by k.  Replays of a captured insert raise
+// it without end (the host counts the slots only between calls), and 0 says
+// that the table is empty, so it stops at its largest value.
+__device__ __forceinline__ void raise_used(Meta* m, uint32_t k) {
+  const uint32_t used = m->used;
+  m->used = k > ~used ? ~0u : used + k;
+}
+
 // Copies the counters a host reader tracks to the table's mirror, if any: t and
 // the slot counts, and after an insert of n positions its new-key count, which
 // the host uses to choose the next insert's claim variant.  Vector stores to

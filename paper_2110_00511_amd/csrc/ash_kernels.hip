@@ -605,11 +605,11 @@ __device__ __forceinline__ void finalize_total(Meta* m, uint32_t cap, int mode, 
     const bool overflow = m->fail != 0 || (check && m->claims > cap - m->t);
     if (!overflow) {
       m->t += total;
-      m->used += total;
+      raise_used(m, total);
       m->result = total;
     } else {
       m->result = 0;
-      m->used += n;  // claimed slots were rolled back to tombstones
+      raise_used(m, n);  // claimed slots were rolled back to tombstones
       m->tombs += n;
       if (!silent)
         __hip_atomic_fetch_or(&m->status, m->fail ? kStatusTableFull : kStatusCapacity, __ATOMIC_RELAXED,

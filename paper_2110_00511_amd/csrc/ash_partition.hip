@@ -949,7 +949,7 @@ __global__ __launch_bounds__(kBlock) void k_part_commit(PartPlan pl, PartRanks p
       __hip_atomic_fetch_or(&meta->status, kStatusCapacity, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       meta->t = t0 + total;
-      meta->used += total;  // a bound: tombstones may be taken
+      raise_used(meta, total);  // a bound: tombstones may be taken
       meta->result = total;
     }
     publish_counts(tb, meta, pl.n);

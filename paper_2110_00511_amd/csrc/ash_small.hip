@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kThreads) void k_insert_small(TableRef tb, BatchKey
                             __HIP_MEMORY_SCOPE_AGENT);
     } else {
       meta->t = t0 + total;
-      meta->used += total;  // a bound: tombstones may be taken
+      raise_used(meta, total);  // a bound: tombstones may be taken
       meta->result = total;
     }
     publish_counts(tb, meta, n);

@@ -173,3 +173,40 @@ def test_width_4_replayed(ash):
         assert torch.equal(m.active_indices().long(), live)
         assert torch.equal(m.key_buffer()[live], eager.key_buffer()[live])
         assert torch.equal(m.heap_buffer(), eager.heap_buffer())
+
+
+@pytest.mark.parametrize("small", [False, True])
+def test_the_bound_on_used_slots_does_not_wrap(ash, small):
+    """Replays raise the bound on the slots in use by every new key and never
+    lower it; past 2^32 it must not read as an empty table, whose parts an
+    insert by bins writes whole."""
+    n = INSERT_MIN + 13
+    m = ash.HashSet(2 * n, 3)
+    a, b = draw(20, n, 3, 0.5 * n), draw(21, n, 3, 0.5 * n) + 5000
+    few = draw(22, 1000, 3, 10_000) + 100_000
+    m.activate(a)  # (the workspace)
+    new_a = m.size()
+    m.clear()
+    new_few = len(torch.unique(few, dim=0))
+    torch.cuda.synchronize()
+    keys = a.clone()
+    graph, graph_few = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        m.activate(keys)
+    with torch.cuda.graph(graph_few):
+        m.activate(few)
+    live = draw(23, 3000, 3, 100_000) + 200_000
+    m.clear()
+    m.activate(live)
+    t = m.size()
+    meta, = [w for w in (v.view(torch.int32) for v in m._alloc.blocks.values() if v.numel() == 256)
+             if w[0].item() == t and w[2].item() == t]
+    meta[2] = -(new_few if small else new_a)  # as after as many replays as it takes: 2^32 less the next one's new keys
+    torch.cuda.synchronize()
+    (graph_few if small else graph).replay()
+    keys.copy_(b)
+    graph.replay()
+    for k in (live, b, few if small else a):
+        assert bool(m.find(k)[1].all())
+    assert m.device_status() == 0
+    assert m.size() == len(torch.unique(torch.cat([live, b, few if small else a]), dim=0))
